@@ -4,16 +4,15 @@
 // Layer 1 (n x d) . (d x 256) is the one dense contraction of the method:
 // bf16 products (exact) summed in fp32 by v_mfma_f32_32x32x16_bf16.  A
 // workgroup of 8 waves (two per SIMD, so that one issues MFMAs while the other
-// waits on LDS or the barrier) computes a 128 x 128 tile, each wave 64 rows x
-// 32 columns (two 32 x 32 blocks).
+// waits on LDS or the barrier) computes a 128 x 128 or 64 x 64 tile of one of
+// four k slices.
 // The sum over k is order-free, so A and B may share any permutation of k:
 // lane l (row / column l mod 32, half l / 32) supplies, in a 64-wide k step,
-// the 32 contiguous values of its half (64 bytes, four 16-byte loads), and
-// MFMA m of the step takes values 8m .. 8m + 7 of both operands.  The next
-// step's loads are issued before this step's four MFMAs.  Tiles are ordered
-// so that the four column tiles of a row tile land on the same XCD (block
-// ids go round-robin over the 8 XCDs) and read the same hidden-state rows
-// through one L2.
+// the 32 contiguous values of its half (64 bytes, four 16-byte pieces), and
+// MFMA m of the step takes values 8m .. 8m + 7 of both operands.  Tiles are
+// ordered so that the workgroups of a row tile land on the same XCD (block ids
+// go round-robin over the 8 XCDs) and read the same hidden-state rows through
+// one L2; giving each XCD its own part of W1 instead was slower at every size.
 //
 // Layers 2 and 3 are fp32: v_mfma_f32_16x16x4f32 for (16 rows x 256) . (256 x
 // 64) in a workgroup of 8 waves (each a k eighth of all 16 rows, loaded once
@@ -28,148 +27,173 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+// a native vector: the HIP struct type is kept in memory when a struct of it is passed around
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-constexpr int L1_TILE = 128;       // rows and columns of a workgroup's tile
-
-constexpr int L1_THREADS = 512;  // 8 waves, each 64 x 32 (2 x 1 MFMA blocks of 32 x 32)
-constexpr int L1_RPT = L1_TILE / (L1_THREADS / 8);  // tile rows a thread moves per step (2)
-
+constexpr int L1_THREADS = 512;  // 8 waves: a quadrant of the tile and a half of each step's k each
 constexpr int KSTEP = 64;          // k per step
 constexpr int KSPLIT = 4;          // k slices (workgroups per tile); their sums meet in layer 2
-constexpr int L1_NS = 2;           // steps in flight in registers (even; 4 measured slower)
 constexpr int LDS_ROW16 = 9;       // LDS row of a tile: 128 bytes of k + 16 bytes of padding
 constexpr int L23_THREADS = 512;   // 8 waves: one k eighth each, both layer-2 column halves
 constexpr int L23_ROWS = 16;
 
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v)
+__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v)
 {
     bf16x8 r;
     __builtin_memcpy(&r, &v, sizeof(r));
     return r;
 }
 
-// One step (64 k) of a thread's share of the A and B tiles: rows j = 0, 1.
+// One step (64 k) of a thread's share of the A and B tiles.
+template <int RPT>
 struct Stage {
-    uint4 a0, a1, b0, b1;
+    u32x4 a[RPT], b[RPT];
 };
 
-__device__ __forceinline__ void load_stage(Stage &x, const uint4 *ga0, const uint4 *ga1, const uint4 *gb0,
+// A step past the end loads the last one again (in bounds; it is never
+// multiplied).  Nothing may touch the loaded values here: an operation on them
+// makes the compiler wait for the loads it has just issued.
+template <int RPT>
+__device__ __forceinline__ void load_stage(Stage<RPT> &x, const u32x4 *const (&ga)[RPT], const u32x4 *gb,
                                            long long bstride, int step, int nsteps)
 {
-    // a step past the end loads the last one (in bounds) and is zeroed, so
-    // that multiplying it adds nothing
-    const bool in = step < nsteps;
-    const int o = (in ? step : nsteps - 1) * (KSTEP / 8);
-    const uint32_t mk = in ? 0xFFFFFFFFu : 0u;  // a mask, not a select (a select of vectors
-                                                // is turned into a scratch lookup)
-    auto m = [mk](uint4 v) { return make_uint4(v.x & mk, v.y & mk, v.z & mk, v.w & mk); };
-    x.a0 = m(ga0[o]);
-    x.a1 = m(ga1[o]);
-    x.b0 = m(gb0[o]);
-    x.b1 = m(gb0[bstride + o]);
-}
-
-__device__ __forceinline__ void put_stage(const Stage &x, uint4 *la, uint4 *lb, int ls, int lstride)
-{
-    la[ls] = x.a0;
-    la[ls + lstride] = x.a1;
-    lb[ls] = x.b0;
-    lb[ls + lstride] = x.b1;
-}
-
-// The 8 MFMAs of one step for a wave's 64 x 32 block (2 x 1 blocks).
-__device__ __forceinline__ void mfma_step(floatx16 (&acc)[2], const uint4 *tla, const uint4 *tlb, int wr, int wc,
-                                          int orow, int och)
-{
-    const uint4 *la = tla + (wr * 64 + orow) * LDS_ROW16 + och;
-    const uint4 *lb = tlb + (wc * 32 + orow) * LDS_ROW16 + och;
+    const int o = (step < nsteps ? step : nsteps - 1) * (KSTEP / 8);
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const bf16x8 a0 = as_bf16x8(la[m]), a1 = as_bf16x8(la[32 * LDS_ROW16 + m]);
-        const bf16x8 b0 = as_bf16x8(lb[m]);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc[1], 0, 0, 0);
+    for (int j = 0; j < RPT; ++j) x.a[j] = ga[j][o];
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) x.b[j] = gb[j * bstride + o];
+}
+
+template <int RPT>
+__device__ __forceinline__ void put_stage(const Stage<RPT> &x, u32x4 *la, u32x4 *lb, int ls)
+{
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        la[ls + j * 64 * LDS_ROW16] = x.a[j];
+        lb[ls + j * 64 * LDS_ROW16] = x.b[j];
     }
 }
 
-// One workgroup per compute unit (its LDS alone rules out three), two waves
-// per SIMD.
+// Layer 1, TILE x TILE tiles (128 or 64), one k slice of a tile per workgroup.
+// A wave computes one quadrant of the tile over half of each step's k (the
+// halves are added at the end): per step a workgroup then reads TILE / 2 rows
+// of each operand 8 times from LDS, half a row each, two thirds of what 64 x 32
+// blocks over the whole k read, and LDS bandwidth is what bounds a step.
+template <int TILE>
 __global__ void __launch_bounds__(L1_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_pred_l1(int n, int d, const uint16_t *h, const uint16_t *w1,
-                                                       float *part, int row_tiles)
+k_pred_l1(int n, int d, const uint16_t *h, const uint16_t *w1, float *part, int row_tiles)
 {
-    // LDS: two stages of the A tile (128 rows) and the B tile (128 columns),
+    constexpr int RPT = TILE / 64;  // rows of each tile a thread moves per step
+    constexpr int NB = TILE / 64;   // 32-wide MFMA blocks per side of a quadrant
+    // LDS: two stages of the A tile (TILE rows) and the B tile (TILE columns),
     // 64 k each, rows padded to 144 bytes so that the 32 rows one MFMA operand
     // read touches spread over the banks
-    __shared__ uint4 lds[2][2][L1_TILE * LDS_ROW16];
+    __shared__ u32x4 lds[2][2][TILE * LDS_ROW16];
+    static_assert(sizeof(lds) >= L1_THREADS * NB * NB * 8 * sizeof(float), "the k halves meet in the tile buffers");
+    constexpr int CT = SAE_PRED_H1 / TILE;             // column tiles
     const int bid = blockIdx.x;
     const int xcd = bid & 7, slot = bid >> 3;
     const int ks = slot % KSPLIT;                      // k slice
-    const int ct = (slot / KSPLIT) % (SAE_PRED_H1 / L1_TILE);
-    const int rt = (slot / KSPLIT / (SAE_PRED_H1 / L1_TILE)) * 8 + xcd;
+    const int ct = (slot / KSPLIT) % CT;
+    const int rt = (slot / KSPLIT / CT) * 8 + xcd;
     if (rt >= row_tiles) return;                      // the whole workgroup
     const int tid = threadIdx.x;
     const int lane = (int)__lane_id(), wave = tid / SAE_WAVE;
-    const int wr = wave >> 2, wc = wave & 3;           // this wave's 64 rows x 32 columns
+    const int wr = (wave >> 1) & 1, wc = wave & 1, kh = wave >> 2;
     const int kper = d / KSPLIT;                       // a multiple of 64
     const int kbeg = ks * kper, nsteps = kper / KSTEP;
-    // global -> LDS: thread t moves 16-byte chunks of rows t / 8 + 64 j (j < 2),
+    // global -> LDS: thread t moves 16-byte chunks of rows t / 8 + 64 j (j < RPT),
     // chunk t mod 8 of each row's 128 bytes, of both tiles
-    static_assert(L1_RPT == 2, "two tile rows per thread and step");
     const int lr = tid >> 3, lc = tid & 7;
-    const uint4 *ga0, *ga1;
-    {
-        auto arow = [&](int j) {
-            int r = rt * L1_TILE + lr + 64 * j;
-            r = r < n ? r : n - 1;  // rows past n repeat row n - 1 (results dropped)
-            return reinterpret_cast<const uint4 *>(h + (long long)r * d + kbeg) + lc;
-        };
-        ga0 = arow(0);
-        ga1 = arow(1);
+    const u32x4 *ga[RPT];
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        int r = rt * TILE + lr + 64 * j;
+        r = r < n ? r : n - 1;  // rows past n repeat row n - 1 (results dropped)
+        ga[j] = reinterpret_cast<const u32x4 *>(h + (long long)r * d + kbeg) + lc;
     }
-    const uint4 *gb0 = reinterpret_cast<const uint4 *>(w1 + (long long)(ct * L1_TILE + lr) * d + kbeg) + lc;
-    const long long bstride = 64ll * d / 8;  // 64 rows of W1, in uint4
-    const int ls = lr * LDS_ROW16 + lc, lstride = 64 * LDS_ROW16;
-    floatx16 acc[2];
+    const u32x4 *gb = reinterpret_cast<const u32x4 *>(w1 + (long long)(ct * TILE + lr) * d + kbeg) + lc;
+    const long long bstride = 64ll * d / 8;  // 64 rows of W1, in u32x4
+    const int ls = lr * LDS_ROW16 + lc;
+    floatx16 acc[NB][NB];
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int bi = 0; bi < NB; ++bi)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[bi][i] = 0.0f;
+        for (int bj = 0; bj < NB; ++bj)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[bi][bj][i] = 0.0f;
     // operand reads: lane (row / column l mod 32, half l / 32) takes, in MFMA
-    // m of a step, the 16 bytes at k = 32 half + 8 m of its row
-    const int orow = lane & 31, och = (lane >> 5) * 4;
-    // pipeline: step s is in LDS buffer s mod 2 while steps s + 1 .. s + L1_NS
-    // are in flight in L1_NS register stages (the loop is unrolled by L1_NS so
-    // that each stage is a fixed set of registers; a step past the end is all
-    // zeros).  Step t >= 1 travels in stage (t - 1) mod L1_NS.
-    Stage sg[L1_NS];
-    load_stage(sg[0], ga0, ga1, gb0, bstride, 0, nsteps);
-    put_stage(sg[0], lds[0][0], lds[0][1], ls, lstride);
-#pragma unroll
-    for (int j = 0; j < L1_NS; ++j) load_stage(sg[j], ga0, ga1, gb0, bstride, 1 + j, nsteps);
+    // m of a step, the 16 bytes at k = 32 half + 8 m of its row; this wave's
+    // m are 2 kh and 2 kh + 1
+    const int oa = (wr * (TILE / 2) + (lane & 31)) * LDS_ROW16 + (lane >> 5) * 4 + 2 * kh;
+    const int ob = (wc * (TILE / 2) + (lane & 31)) * LDS_ROW16 + (lane >> 5) * 4 + 2 * kh;
+    // pipeline: step s is in LDS buffer s mod 2 while steps s + 1 and s + 2 are
+    // in flight in registers.  Four steps in flight, and the next step's
+    // operands read from LDS during this step's MFMAs, were no faster: what is
+    // left is the rate at which a compute unit is fed from L2
+    Stage<RPT> s0, s1;
+    load_stage(s0, ga, gb, bstride, 0, nsteps);
+    put_stage(s0, lds[0][0], lds[0][1], ls);
+    load_stage(s0, ga, gb, bstride, 1, nsteps);
+    load_stage(s1, ga, gb, bstride, 2, nsteps);
     __syncthreads();
-    for (int st = 0; st < nsteps; st += L1_NS) {
+    auto step = [&](Stage<RPT> &x, int b, int t) {  // step t, in LDS buffer b; x holds step t + 1
+        bf16x8 va[2][NB], vb[2][NB];
 #pragma unroll
-        for (int j = 0; j < L1_NS; ++j) {
-            const int b = j & 1;  // st is a multiple of L1_NS (even)
-            mfma_step(acc, lds[b][0], lds[b][1], wr, wc, orow, och);                  // step st + j
-            put_stage(sg[j], lds[b ^ 1][0], lds[b ^ 1][1], ls, lstride);              // step st + j + 1
-            load_stage(sg[j], ga0, ga1, gb0, bstride, st + j + 1 + L1_NS, nsteps);
-            __syncthreads();
-        }
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                va[m][i] = as_bf16x8(lds[b][0][oa + i * 32 * LDS_ROW16 + m]);
+                vb[m][i] = as_bf16x8(lds[b][1][ob + i * 32 * LDS_ROW16 + m]);
+            }
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int bi = 0; bi < NB; ++bi)
+#pragma unroll
+                for (int bj = 0; bj < NB; ++bj)
+                    acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[m][bi], vb[m][bj], acc[bi][bj], 0, 0, 0);
+        put_stage(x, lds[b ^ 1][0], lds[b ^ 1][1], ls);
+        load_stage(x, ga, gb, bstride, t + 3, nsteps);
+        __syncthreads();
+    };
+    int st = 0;
+    for (; st + 2 <= nsteps; st += 2) {
+        step(s0, 0, st);
+        step(s1, 1, st + 1);
     }
+    if (st < nsteps) step(s0, 0, st);  // uniform
+    // the two k halves of a quadrant: each wave hands half of its sums to the
+    // other (through the tile buffers, free since the last barrier) and
+    // finishes the half it keeps, first half of k + second half
+    constexpr int E = NB * NB * 16, HE = E / 2;
+    float mine[HE], give[HE];
+#pragma unroll
+    for (int e = 0; e < HE; ++e) {
+        const float lo = acc[e / 16 / NB][(e / 16) % NB][e % 16];
+        const float hi = acc[(e + HE) / 16 / NB][((e + HE) / 16) % NB][(e + HE) % 16];
+        mine[e] = kh ? hi : lo;
+        give[e] = kh ? lo : hi;
+    }
+    float *xs = reinterpret_cast<float *>(lds);  // [wave][HE][64]
+#pragma unroll
+    for (int e = 0; e < HE; ++e) xs[(wave * HE + e) * SAE_WAVE + lane] = give[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < HE; ++e) mine[e] = mine[e] + xs[((wave ^ 4) * HE + e) * SAE_WAVE + lane];
     // partial sums of this k slice; C layout: lane l holds column l mod 32,
     // rows 8 (i / 4) + 4 (l / 32) + i mod 4 of each 32 x 32 block
-    float *out = part + (long long)ks * n * SAE_PRED_H1;
-    const int col = ct * L1_TILE + wc * 32 + (lane & 31);
+    float *out = part + (long long)ks * n * SAE_PRED_H1 + ct * TILE + wc * (TILE / 2) + (lane & 31);
+    const int r0 = rt * TILE + wr * (TILE / 2) + (lane >> 5) * 4;
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int r = rt * L1_TILE + wr * 64 + bi * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-            if (r < n) out[(long long)r * SAE_PRED_H1 + col] = acc[bi][i];
-        }
+    for (int e = 0; e < HE; ++e) {
+        // element e of the kept half: block (bi, bj), register i
+        const int bi = (NB == 2) ? kh : 0, bj = (NB == 2) ? e / 16 : 0;
+        const int i = (NB == 2) ? e % 16 : e + kh * HE;
+        const int r = r0 + bi * 32 + (i >> 2) * 8 + (i & 3);
+        if (r < n) out[(long long)r * SAE_PRED_H1 + bj * 32] = mine[e];
+    }
 }
 
 __global__ void __launch_bounds__(L23_THREADS) __attribute__((amdgpu_waves_per_eu(1, 2)))
@@ -208,6 +232,14 @@ k_pred_l23(int n, const float *part, const float *b1, const float *w2, const flo
             bw[cb][u] = reinterpret_cast<const float4 *>(w2 + (long long)(cb * 16 + (lane & 15)) * SAE_PRED_H1 + kb)[u];
         c[u] = pc[u];
     }
+    // what the end needs, with the same round trip
+    float bias[NCB], wt[NCB];
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+        bias[cb] = b2[cb * 16 + (lane & 15)];
+        wt[cb] = w3[cb * 16 + (lane & 15)];
+    }
+    const float bias3 = b3[0];
     __builtin_amdgcn_sched_barrier(0);
     floatx4 acc[NCB];
 #pragma unroll
@@ -257,15 +289,13 @@ k_pred_l23(int n, const float *part, const float *b1, const float *w2, const flo
         for (int i = 0; i < 4; ++i) t[i] = 0.0f;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
-            const int col = cb * 16 + (lane & 15);
-            const float bias = b2[col], wt = w3[col];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float h2 = acc[cb][i];
 #pragma unroll
                 for (int q = 0; q < NW - 1; ++q) h2 = h2 + hsum[q][cb * 4 + i][lane];
-                h2 = h2 + bias;
-                t[i] = t[i] + wt * (h2 > 0.0f ? h2 : 0.0f);
+                h2 = h2 + bias[cb];
+                t[i] = t[i] + wt[cb] * (h2 > 0.0f ? h2 : 0.0f);
             }
         }
 #pragma unroll
@@ -280,7 +310,7 @@ k_pred_l23(int n, const float *part, const float *b1, const float *w2, const flo
     __syncthreads();
     if (threadIdx.x < L23_ROWS) {
         const int r = r0 + threadIdx.x;
-        const float y = ysum[threadIdx.x] + b3[0];
+        const float y = ysum[threadIdx.x] + bias3;
         if (r < n) {
             logit[r] = y;
             if (pred) pred[r] = y > 0.0f ? 1 : 0;
@@ -320,14 +350,26 @@ hipError_t predict_scratch(float **out)
     return hipSuccess;
 }
 
+// Up to 2,048 rows the 128-wide tiles are at most 128 workgroups, half of the
+// compute units, and a workgroup's time is its bytes over what one unit is fed
+// (about 50-70 KB/us): 64-wide tiles halve those bytes and quadruple the
+// workgroups.  Layer 1 at d = 4,096, 64- against 128-wide: 5.2 / 10.5 us at 1
+// row, 6.7 / 12.3 at 256, 7.9 / 12.9 at 1,024, 13.2 / 13.6 at 2,048, 22.8 /
+// 15.8 at 4,096 (there the 64-wide tiles move twice the bytes).
+constexpr int L1_64_MAX_ROWS = 2048;
+
 hipError_t launch_predict(int n, int d, const uint16_t *h, const uint16_t *w1, const float *b1, const float *w2,
                           const float *b2, const float *w3, const float *b3, float *work, float *logit,
                           uint8_t *pred, hipStream_t s)
 {
-    const int row_tiles = (n + L1_TILE - 1) / L1_TILE;
+    const int tile = n <= L1_64_MAX_ROWS ? 64 : 128;
+    const int row_tiles = (n + tile - 1) / tile;
     const int groups = (row_tiles + 7) / 8;  // rounds of 8 row tiles, one per XCD
-    const int per_tile = KSPLIT * (SAE_PRED_H1 / L1_TILE);
-    hipLaunchKernelGGL(k_pred_l1, dim3(groups * 8 * per_tile), dim3(L1_THREADS), 0, s, n, d, h, w1, work, row_tiles);
+    const dim3 grid(groups * 8 * KSPLIT * (SAE_PRED_H1 / tile));
+    if (tile == 64)
+        hipLaunchKernelGGL(k_pred_l1<64>, grid, dim3(L1_THREADS), 0, s, n, d, h, w1, work, row_tiles);
+    else
+        hipLaunchKernelGGL(k_pred_l1<128>, grid, dim3(L1_THREADS), 0, s, n, d, h, w1, work, row_tiles);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_pred_l23, dim3((n + L23_ROWS - 1) / L23_ROWS), dim3(L23_THREADS), 0, s, n, work, b1, w2, b2,

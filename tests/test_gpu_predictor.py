@@ -59,6 +59,14 @@ def test_predictor_matches_oracle(n, d):
         % (n, d, err.max(), float(np.max(np.abs(g1 - h1) / (1 + np.abs(h1)))), 100 * gp.mean()))
 
 
+# layer-1 tiles are 64 wide up to 2,048 rows and 128 wide beyond; a k slice takes d / 256 steps (odd and even)
+@pytest.mark.parametrize("n,d", [(63, 256), (64, 768), (65, 1280), (129, 512), (2048, 256), (2049, 768), (2177, 512)])
+def test_predictor_tile_edges(n, d):
+    y, h1, _, g1, gy, _ = run(n, d, 77 + n + d)
+    assert np.all(np.abs(g1 - h1) <= TOL * (1 + np.abs(h1))), np.max(np.abs(g1 - h1))
+    assert np.all(np.abs(gy.astype(np.float64) - y) <= TOL * (1 + np.abs(y)))
+
+
 def test_predictor_argument_checks():
     w = {k: torch.zeros(8, dtype=torch.float32, device="cuda") for k in ("b1", "w2", "b2", "w3", "b3")}
     w["w1"] = torch.zeros((256, 64), dtype=torch.int16, device="cuda")
