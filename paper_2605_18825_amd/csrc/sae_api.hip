@@ -580,12 +580,9 @@ sae_status sae_insert_blocks(sae_ctx *c, int32_t n, const int32_t *inst, const i
         return fail(c, SAE_ERR_ARG, "ids, hash, parent, last_access, meta, off must be non-NULL");
     hipError_t e = launch_insert(c->dc, n, inst, ids, hash, parent, last_access, meta, off, c->skip, S(stream));
     if (e != hipSuccess) return hip_fail(c, e, "sae_insert_blocks");
-    c->ghost_tombs += n;
-    if (c->ghost_tombs > 0.25 * (double)c->ghost_slots) {
-        e = launch_ghost_rebuild(c->dc, S(stream));
-        if (e != hipSuccess) return hip_fail(c, e, "ghost rebuild");
-        c->ghost_tombs = 0;
-    }
+    // Add() takes no slot of recently_evicted's table (a consumed entry leaves
+    // its slot as it was), so it does not bring the table's rebuild nearer:
+    // only the victims of a decision fill slots, at most max_k of an instance
     return SAE_OK;
 }
 
