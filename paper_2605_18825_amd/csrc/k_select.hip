@@ -1491,7 +1491,6 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
 #define FIN_GPQ (SAE_NBUCKET / FIN_G)        // group workgroups per queue
 #define FIN_NU 64                            // union workgroups
 #define FIN_GCAP 4096                        // candidates a workgroup ranks at once
-#define FIN_U (SAE_LCAP / FIN_THREADS)       // candidates per thread of one streamed queue
 #define FIN_STACK 80                         // pending ranges (a range splits into two)
 #define FIN_SB 64                            // sub-bins per bucket in the ranking
 #define FIN_T 64                             // largest segment ranked by comparison alone
@@ -1549,7 +1548,7 @@ __device__ void fin_info(const DevCtx &c, const SelectArgs &a, int inst, uint32_
             const bool all = f.thr[q] == ~0ull;
             const uint32_t need = (all && f.C[q] < kq) ? f.C[q] : kq;
             const bool fail = need > 0 && ((a.flags & SAE_SS_FORCE_FALLBACK) || f.nb[q] <= 0 || f.C[q] < need ||
-                                           f.over[q] > 0 || f.C[q] > SAE_LCAP);
+                                           f.over[q] > 0);
             f.need[q] = need;
             f.fail[q] = fail ? 1 : 0;
             any |= fail ? 1 : 0;

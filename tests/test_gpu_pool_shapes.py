@@ -1,0 +1,84 @@
+"""Pool shapes at which the scan's aligned reads, the batched engine's two
+selections and the candidate stripes can go wrong, against the oracle:
+instances that start at every offset mod 4 and end inside a group of four
+blocks, and a k at the limit of the candidate stripes."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+import oracle  # noqa: E402
+import synth  # noqa: E402
+import torch  # noqa: E402
+from harness import Pair, say  # noqa: E402
+from paper_2605_18825_amd import api  # noqa: E402
+from paper_2605_18825_amd.pool import DevicePool, SelectBuffers  # noqa: E402
+
+
+def several(n_inst, N, k, flags, layout="large", seed=31, edit=None, k_per=None, mix=None):
+    """n_inst pools in one context: lists, scores, decisions equal the oracle's."""
+    cfg = synth.pool_config(layout, n_blocks=N, k=k, **({} if mix is None else dict(mix=mix)))
+    Q = len(cfg["kinds"])
+    ctx = api.sae_create(n_inst, N, cfg["kinds"], max_k=k)
+    try:
+        dp, ocs = DevicePool(n_inst, N), []
+        for i in range(n_inst):
+            pool = synth.make_pool(cfg, seed=seed + i, n_blocks=N)
+            if edit is not None:
+                edit(pool, np.random.default_rng(seed + i))
+            dp.fill_instance(i, pool)
+            oc = oracle.OracleCache(N, cfg["kinds"], oracle.Params(Q, mu=cfg["mu"], sigma=cfg["sigma"], K=k))
+            oc.bind(pool["last_access"], pool["queue"], oracle.block_type(pool["counts"]), pool["ntok"], pool["ob"],
+                    pool["omax"], pool["valid"], pool["ref_count"], pool["parent"], pool["hash"])
+            ocs.append(oc)
+        dp.bind(ctx)
+        api.sae_index_build(ctx)
+        api.sae_set_params(ctx, -1, api.make_params(Q, mu=cfg["mu"], sigma=cfg["sigma"], K=k))
+        out = SelectBuffers(n_inst, Q, k)
+        now = synth.pools.NOW
+        kd = None if k_per is None else torch.as_tensor(np.asarray(k_per, np.int32)).cuda()
+        out.run(ctx, now, k, flags, k_per_inst=kd)
+        torch.cuda.synchronize()
+        for i, oc in enumerate(ocs):
+            ki = k if k_per is None else k_per[i]
+            lists, key, dec = oc.score_select(now, ki)
+            for q in range(Q):
+                c = int(out.count[i, q])
+                assert c == len(lists[q]), (i, q, c, len(lists[q]))
+                assert np.array_equal(out.victims[i, q, :c].cpu().numpy(), lists[q]), (i, q)
+                got = out.scores[i, q, :c].cpu().numpy().view(np.uint32)
+                assert np.array_equal(got, key[lists[q]]), (i, q)
+            d = int(out.decision_count[i])
+            assert np.array_equal(out.decision[i, :d].cpu().numpy(), dec), i
+        return api.status_names(api.sae_poll_status(ctx))
+    finally:
+        api.sae_destroy(ctx)
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 255, 257, 1001, 4098, 16387])
+def test_scan_instances_at_every_alignment(N):
+    say("scan: 5 instances of %d blocks" % N)
+    several(5, N, max(1, min(64, N)), api.SS_ENGINE_SCAN)
+
+
+def test_scan_large_odd_pool():
+    """An odd size at which a wave reads several batches."""
+    say("scan: 700,001 blocks")
+    assert several(1, 700001, 1000, api.SS_ENGINE_SCAN) == []
+
+
+def test_largest_k_without_fallback():
+    """k = 8,192 on 4M blocks: about 16,000 candidates per queue, more than the
+    stripes alone hold; their overflow list takes the rest and the exact slow
+    path stays out."""
+    cfg = synth.pool_config("large")
+    say("k = 8,192: generating pool")
+    pool = synth.make_pool(cfg, seed=88)
+    p = Pair(cfg["kinds"], pool, 8192, mu=cfg["mu"], sigma=cfg["sigma"], K=8192)
+    try:
+        for t in (0, 400, 800):
+            say("k = 8,192: score_select")
+            p.select(pool["now"] + t, 8192)
+        assert not p.status()
+    finally:
+        p.close()
