@@ -44,16 +44,52 @@ __device__ __forceinline__ unsigned long long lanemask_lt()
     return (l == 0) ? 0ull : (~0ull >> (64 - l));
 }
 
+// A lane's value moved by the DPP control CTRL (rows of the mask only); lanes
+// without a source take `idle`.  One VALU operation, where a shuffle is an LDS
+// round trip.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t idle, uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)idle, (int)v, CTRL, ROWS, 0xF, false);
+}
+#define DPP_SHR(n) (0x110 + (n))  // from the lane n below, inside rows of 16
+#define DPP_BCAST15 0x142         // lane 15 of a row to the next row
+#define DPP_BCAST31 0x143         // lane 31 to the upper half
+
+// Combination of a wave's values up to and including each lane's (idle: the
+// neutral element); lane 63 holds the wave's.
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_incl(uint32_t v, uint32_t idle, Op op)
+{
+    v = op(v, dpp_move<DPP_SHR(1)>(idle, v));
+    v = op(v, dpp_move<DPP_SHR(2)>(idle, v));
+    v = op(v, dpp_move<DPP_SHR(4)>(idle, v));
+    v = op(v, dpp_move<DPP_SHR(8)>(idle, v));
+    v = op(v, dpp_move<DPP_BCAST15, 0xA>(idle, v));
+    v = op(v, dpp_move<DPP_BCAST31, 0xC>(idle, v));
+    return v;
+}
+
 // Inclusive scan of v over a wave.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
 {
-    int l = lane_id();
-#pragma unroll
-    for (int d = 1; d < SAE_WAVE; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, SAE_WAVE);
-        if (l >= d) v += t;
-    }
-    return v;
+    return wave_incl(v, 0u, [](uint32_t x, uint32_t y) { return x + y; });
+}
+
+// Sum, minimum and maximum over a wave (the same on every lane).
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), SAE_WAVE - 1);
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v)
+{
+    v = wave_incl(v, 0xFFFFFFFFu, [](uint32_t x, uint32_t y) { return x < y ? x : y; });
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, SAE_WAVE - 1);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    v = wave_incl(v, 0u, [](uint32_t x, uint32_t y) { return x > y ? x : y; });
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, SAE_WAVE - 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -74,33 +110,38 @@ __device__ void find_crossing(const uint32_t *hist, int nq, const uint32_t *rem,
     const int tid = threadIdx.x;
     const int q = tid >> 7;
     const int seg = tid & 127;
+    uint32_t h[16];  // this thread's bins (read once, 16 bytes at a time)
     uint32_t s = 0;
-    if (q < nq) {
-        const uint32_t *h = hist + q * SAE_BINS + seg * 16;
+    const bool mine = q < nq && active[q];
+    const uint32_t r = mine ? rem[q] : 0u;
+    {
+        const uint4 *h4 = reinterpret_cast<const uint4 *>(hist + (q < nq ? q : 0) * SAE_BINS + seg * 16);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s += h[i];
+        for (int i = 0; i < 4; ++i) {
+            const uint4 v = h4[i];
+            h[4 * i] = v.x;
+            h[4 * i + 1] = v.y;
+            h[4 * i + 2] = v.z;
+            h[4 * i + 3] = v.w;
+        }
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += h[i];
     uint32_t incl = wave_incl_scan(s);
     const int w = tid >> 6;
     if (lane_id() == 63) seg_tot[w] = incl;
     lds_barrier();
     if ((w & 1) == 1) incl += seg_tot[w - 1];
-    uint32_t excl = incl - s;
-    if (q < nq && active[q]) {
-        uint32_t r = rem[q];
-        if (excl < r && r <= incl) {
-            const uint32_t *h = hist + q * SAE_BINS + seg * 16;
-            uint32_t run = excl;
-            for (int i = 0; i < 16; ++i) {
-                uint32_t c = h[i];
-                if (run < r && r <= run + c) {
-                    out[q].bin = seg * 16 + i;
-                    out[q].below = run;
-                    out[q].cnt = c;
-                    break;
-                }
-                run += c;
+    uint32_t run = incl - s;
+    if (mine && run < r && r <= incl) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            if (run < r && r <= run + h[i]) {
+                out[q].bin = seg * 16 + i;
+                out[q].below = run;
+                out[q].cnt = h[i];
             }
+            run += h[i];
         }
     }
     lds_barrier();
@@ -412,6 +453,128 @@ __device__ int merge_decision(const unsigned long long *lists, int stride, const
         }
     }
     return n1 + min(rest, total);
+}
+
+// merge_decision for lists in LDS, Q segments of Pe (a power of two) elements:
+// one element per thread and step, its searches in the other lists side by
+// side (one LDS round trip per halving for all of them).
+__device__ int merge_decision_lds(const unsigned long long *lists, int Pe, const int32_t *cnt, int Q, int qe, int k,
+                                  int32_t *dec)
+{
+    const int lp = 31 - __clz(Pe);
+    int cn[SAE_MAX_QUEUES];
+#pragma unroll
+    for (int q = 0; q < SAE_MAX_QUEUES; ++q) cn[q] = q < Q ? cnt[q] : 0;
+    int n1 = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < SAE_MAX_QUEUES; ++q) {
+        n1 = q == qe ? min(k, cn[q]) : n1;
+        total += q == qe ? 0 : cn[q];
+    }
+    const int rest = k - n1;
+    for (int i = threadIdx.x; i < Q << lp; i += blockDim.x) {
+        const int q = i >> lp, j = i & (Pe - 1);
+        if (j >= cnt[q]) continue;
+        const unsigned long long e = lists[i];
+        const int32_t id = (int32_t)(uint32_t)(e & 0xFFFFFFFFull);
+        if (q == qe) {
+            if (j < n1) dec[j] = id;
+            continue;
+        }
+        if (j >= rest) continue;
+        int l[SAE_MAX_QUEUES];
+#pragma unroll
+        for (int q2 = 0; q2 < SAE_MAX_QUEUES; ++q2) l[q2] = 0;
+        for (int st = Pe; st > 0; st >>= 1) {
+#pragma unroll
+            for (int q2 = 0; q2 < SAE_MAX_QUEUES; ++q2) {
+                if (q2 >= Q) break;  // uniform
+                const int t = l[q2] + st;
+                const int tc = t <= cn[q2] ? t : cn[q2];  // an unconditional read inside the segment
+                const unsigned long long v = lists[(q2 << lp) + (tc > 0 ? tc - 1 : 0)];
+                l[q2] = (t <= cn[q2] && v < e) ? t : l[q2];
+            }
+        }
+        int rank = j;
+#pragma unroll
+        for (int q2 = 0; q2 < SAE_MAX_QUEUES; ++q2) rank += (q2 == q || q2 == qe) ? 0 : l[q2];
+        if (rank < rest) dec[n1 + rank] = id;
+    }
+    return n1 + min(rest, total);
+}
+
+// Sort, ascending, of T / S segments of S elements in LDS (S a power of two,
+// T <= 4 blockDim.x; the elements of a segment distinct, unused slots ~0 at
+// its end), blockDim.x = SEL_THREADS.  Runs of 64 (or whole segments shorter
+// than that) are sorted in registers, one element per lane, by a bitonic
+// network; then every element's place is its own in its run plus its counts
+// of smaller elements in the segment's other runs, searched eight at a time.
+// Two barriers whatever the size: 256 x 4 took 10 us as runs of 256 sorted by
+// one wave each.  All threads call.
+__device__ void sort_segments_rank(unsigned long long *a, int T, int S)
+{
+    constexpr int MAXE = 4;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int R = S < SAE_WAVE ? S : SAE_WAVE;  // elements of a run
+    unsigned long long x[MAXE];
+#pragma unroll
+    for (int u = 0; u < MAXE; ++u) {
+        const int i = tid + u * SEL_THREADS;
+        x[u] = i < T ? a[i] : ~0ull;
+        if (u * SEL_THREADS >= T) continue;  // uniform
+#pragma unroll 1
+        for (int k = 2; k <= R; k <<= 1) {
+#pragma unroll 1
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                const unsigned long long y = shfl_xor_u64(x[u], j);
+                const bool low = ((lane & j) == 0) == ((lane & k) == 0 || k == R);
+                x[u] = ((x[u] < y) == low) ? x[u] : y;
+            }
+        }
+        if (i < T) a[i] = x[u];
+    }
+    if (S <= SAE_WAVE) {
+        lds_barrier();
+        return;
+    }
+    lds_barrier();
+    int rank[MAXE];
+    const int nr = S / SAE_WAVE;  // runs per segment
+#pragma unroll
+    for (int u = 0; u < MAXE; ++u) {
+        const int i = tid + u * SEL_THREADS;
+        rank[u] = lane;
+        if (u * SEL_THREADS >= T) continue;  // uniform
+        const int s0 = (i < T ? i : 0) & ~(S - 1);
+        const int own = ((i < T ? i : 0) - s0) / SAE_WAVE;
+#pragma unroll 1
+        for (int g = 0; g < nr; g += 8) {  // uniform
+            int l[8];
+#pragma unroll
+            for (int w = 0; w < 8; ++w) l[w] = 0;
+#pragma unroll
+            for (int st = SAE_WAVE; st > 0; st >>= 1) {
+#pragma unroll
+                for (int w = 0; w < 8; ++w) {
+                    if (g + w < nr) {  // uniform
+                        const int t = l[w] + st;  // st = 64: the whole run is smaller
+                        const int tc = t <= SAE_WAVE ? t : SAE_WAVE;  // an unconditional read
+                        const unsigned long long v = a[s0 + (g + w) * SAE_WAVE + tc - 1];
+                        l[w] = (t <= SAE_WAVE && v < x[u]) ? t : l[w];
+                    }
+                }
+            }
+#pragma unroll
+            for (int w = 0; w < 8; ++w) rank[u] += (g + w < nr && g + w != own) ? l[w] : 0;
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int u = 0; u < MAXE; ++u) {
+        const int i = tid + u * SEL_THREADS;
+        if (i < T && x[u] != ~0ull) a[(i & ~(S - 1)) + rank[u]] = x[u];
+    }
+    lds_barrier();
 }
 
 __device__ __forceinline__ void commit_bookkeeping(InstState &s, int d, bool commit)
@@ -861,7 +1024,7 @@ __device__ uint4 scan_entry(int kind, uint32_t dlo, float aw, uint32_t tk, float
 }
 
 // Scan pruning of a log-normal queue q for blocks of type ty: the smallest
-// D in [0, 2^31] such that every block of (q, ty) with dt < D has a key above
+// D in [0, 2^31] (or a little less) such that every block of (q, ty) with dt < D has a key above
 // the bound key tk (IEEE bits of T >= 0), so the scan need not score it.
 // D is the first dt at which key(dt) <= bits(T') holds, T' = max(T (1 + 2^-15),
 // 2^-100), found by a 64-way bisection with the scan's own key function.
@@ -887,7 +1050,9 @@ __device__ uint32_t lognormal_dt_floor(const ScoreTab &t, int q, int ty, uint32_
     const uint32_t lane = (uint32_t)lane_id();
     uint32_t lo = 0, hi = 0x80000000u;  // the predicate fails at lo (dt = 0 gives +inf) and holds at hi
     uint32_t dummy = 0;
-    while (hi - lo > 1) {
+    // a floor up to lo / 512 short of D prunes all but a few blocks of what D
+    // does (lo + 1 <= D: the predicate still fails at lo)
+    while (hi - lo > 1 && hi - lo > lo >> 9) {
         const uint32_t p = lo + (uint32_t)(((unsigned long long)(hi - lo) * (lane + 1)) >> 6);  // lane 63: hi
         const bool ok = (p >= hi) || key_lognormal((int32_t)p, 0, m, t, dummy) <= tpb;
         const unsigned long long mk = __ballot(ok);
@@ -897,7 +1062,7 @@ __device__ uint32_t lognormal_dt_floor(const ScoreTab &t, int q, int ty, uint32_
         lo = (f == 0) ? lo : prev;
         hi = nhi;
     }
-    return hi;
+    return lo + 1;
 }
 
 // Pool-scan engine, step 2: per (instance, queue), the candidate bound and the
@@ -1226,6 +1391,27 @@ __device__ __forceinline__ bool product_prunes(uint32_t pn, uint32_t pd, float a
     return lhs > rhs;
 }
 
+// The filter's verdict on block b of an instance (meta m, offsets off): true
+// when the block is evictable and the entry e of its (type, queue) cannot
+// prove its (key, id) above the queue's bound.  Every test is evaluated (no
+// short-circuit branches).
+__device__ __forceinline__ bool scan_keep(const uint4 e, uint32_t m, int32_t la, uint32_t off, int32_t b, int32_t now,
+                                          const int32_t *ef_lim, uint32_t &st)
+{
+    const bool ev = (m & (SAE_META_VALID | SAE_META_LEAF | SAE_META_REF)) == (SAE_META_VALID | SAE_META_LEAF);
+    const int32_t dtr = now - la;
+    st |= (ev & (dtr < 0)) ? (uint32_t)SAE_ST_FUTURE_ACCESS : 0u;
+    const int32_t dt = dtr < 0 ? 0 : dtr;
+    const uint32_t ob = off & 0xFFFFu, om = off >> 16;
+    const bool one = ((e.w & 2u) != 0u) | (om == 0u);
+    const uint32_t pn = one ? 1u : (om > ob ? om - ob : 0u);
+    const uint32_t pd = one ? 1u : om;
+    const int32_t lim = ef_lim[(m >> SAE_META_NTOK_SHIFT) & 15u];
+    const bool k_ef = ((e.w & 1u) != 0u) | (b <= lim);
+    const bool k_pr = !product_prunes(pn, pd, __uint_as_float(e.y), __uint_as_float(e.z), dt);
+    return ev & ((uint32_t)dt >= e.x) & k_pr & k_ef;
+}
+
 // Four consecutive blocks of one lane, as loaded from HBM.
 struct Quad {
     int4 la;
@@ -1233,34 +1419,50 @@ struct Quad {
     uint2 m;
 };
 
-__device__ __forceinline__ Quad load_quad_vec(const DevCtx &c, long long e0)
+// The blocks of one instance as aligned groups of four (whatever the pool's
+// size and the instance's offset in it, so that every size reads with vector
+// loads): groups q0 .. q0 + nq - 1 of the pool arrays, the first and the last
+// of which may hold blocks of other instances (quad_mask).  Only the very last
+// group of the arrays can reach past them; it is not among the nvec groups
+// that may be loaded whole.
+struct QuadRange {
+    long long q0;
+    int nq, nvec;
+    int b0;  // block id of the first group's first element (-3 .. 0)
+};
+
+__device__ __forceinline__ QuadRange quad_range(const DevCtx &c, int inst)
 {
-    Quad r;
-    r.la = *reinterpret_cast<const int4 *>(c.la + e0);
-    r.m = *reinterpret_cast<const uint2 *>(c.meta + e0);
-    r.off = *reinterpret_cast<const uint4 *>(c.off + e0);
+    const long long base = (long long)inst * c.N;
+    QuadRange r;
+    r.q0 = base >> 2;
+    r.nq = (int)(((base + c.N + 3) >> 2) - r.q0);
+    const long long whole = ((long long)c.n_inst * c.N >> 2) - r.q0;
+    r.nvec = (long long)r.nq < whole ? r.nq : (int)whole;
+    r.b0 = (int)(r.q0 * 4 - base);
     return r;
 }
 
-// Elements e0 .. e0 + 3 of the instance starting at `base`, those below N.
-__device__ __forceinline__ Quad load_quad_safe(const DevCtx &c, long long base, long long e0, long long N)
+// Group i of the range (0 <= i < nvec).
+__device__ __forceinline__ Quad load_quad_vec(const DevCtx &c, const QuadRange &r, int i)
 {
-    uint32_t m[4] = {0, 0, 0, 0};
-    int32_t l[4] = {0, 0, 0, 0};
-    uint32_t o[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (e0 + j < N) {
-            l[j] = c.la[base + e0 + j];
-            m[j] = c.meta[base + e0 + j];
-            o[j] = c.off[base + e0 + j];
-        }
-    }
-    Quad r;
-    r.la = make_int4(l[0], l[1], l[2], l[3]);
-    r.off = make_uint4(o[0], o[1], o[2], o[3]);
-    r.m = make_uint2(m[0] | (m[1] << 16), m[2] | (m[3] << 16));
-    return r;
+    const long long e0 = (r.q0 + i) * 4;
+    Quad x;
+    x.la = *reinterpret_cast<const int4 *>(c.la + e0);
+    x.m = *reinterpret_cast<const uint2 *>(c.meta + e0);
+    x.off = *reinterpret_cast<const uint4 *>(c.off + e0);
+    return x;
+}
+
+// Blocks b .. b + 3 of a group: those outside 0 .. N - 1 lose their meta (not
+// valid, so never evictable).
+__device__ __forceinline__ void quad_mask(Quad &x, int b, int N)
+{
+    const uint32_t k0 = (uint32_t)b < (uint32_t)N ? 0xFFFFu : 0u, k1 = (uint32_t)(b + 1) < (uint32_t)N ? 0xFFFF0000u : 0u;
+    const uint32_t k2 = (uint32_t)(b + 2) < (uint32_t)N ? 0xFFFFu : 0u,
+                   k3 = (uint32_t)(b + 3) < (uint32_t)N ? 0xFFFF0000u : 0u;
+    x.m.x &= k0 | k1;
+    x.m.y &= k2 | k3;
 }
 
 __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
@@ -1279,19 +1481,19 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
     const int inst = blockIdx.y;
     const int wg = blockIdx.x;
     const int Q = c.Q;
-    const long long N = c.N;
+    const int N = c.N;
     const long long base = (long long)inst * N;
     const int lane = lane_id();
     const int wave = threadIdx.x / SAE_WAVE;
     const int tid = threadIdx.x;
-    const long long nb = (N + SCAN_BATCH - 1) / SCAN_BATCH;
-    const long long nfull = ((N & 3) == 0) ? N / SCAN_BATCH : 0;  // batches read with vector loads
-    const long long gw = (long long)wg * SCAN_WAVES + wave;
-    const long long tw = (long long)gridDim.x * SCAN_WAVES;
+    const QuadRange qr = quad_range(c, inst);
+    const int nfull = (qr.nvec + SAE_WAVE - 1) / SAE_WAVE;  // batches read with vector loads
+    const int gw = wg * SCAN_WAVES + wave;
+    const int tw = (int)gridDim.x * SCAN_WAVES;
     // the first two batches' loads go out before the tables are read
-    auto ld = [&](long long bi) {
-        const long long b = bi < nfull ? bi : nfull - 1;
-        return load_quad_vec(c, base + b * SCAN_BATCH + lane * 4);
+    auto ld = [&](int bi) {
+        const int i = bi * SAE_WAVE + lane;
+        return load_quad_vec(c, qr, i < qr.nvec ? i : qr.nvec - 1);
     };
     Quad qa = {}, qb = {}, qc = {};
     if (nfull > 0) {
@@ -1355,30 +1557,24 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
 
     const unsigned long long lt = lanemask_lt();
     uint32_t nl = 0;  // queued blocks of this wave (wave-uniform)
-    auto process = [&](const Quad &cur, long long bi) {
+    // a batch of 64 groups: the instance's first and last batch may hold blocks
+    // of its neighbours, and the last one lanes past its end
+    auto process = [&](Quad &cur, int bi) {
+        const int i = bi * SAE_WAVE + lane;
+        const int b0 = i * 4 + qr.b0;
+        if (bi == 0 || bi == nfull - 1) {  // wave-uniform
+            quad_mask(cur, b0, N);
+            if (i >= qr.nvec) cur.m = make_uint2(0u, 0u);
+        }
         const int32_t lav[4] = {cur.la.x, cur.la.y, cur.la.z, cur.la.w};
         const uint32_t offv[4] = {cur.off.x, cur.off.y, cur.off.z, cur.off.w};
         const uint32_t mv[4] = {cur.m.x & 0xFFFFu, cur.m.x >> 16, cur.m.y & 0xFFFFu, cur.m.y >> 16};
-        const uint32_t b0 = (uint32_t)(bi * SCAN_BATCH) + (uint32_t)lane * 4u;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint32_t m = mv[j];
-            const uint4 e = ent[m & 63u];
-            const bool ev = (m & (SAE_META_VALID | SAE_META_LEAF | SAE_META_REF)) == (SAE_META_VALID | SAE_META_LEAF);
-            const int32_t dtr = now - lav[j];
-            st |= (ev & (dtr < 0)) ? (uint32_t)SAE_ST_FUTURE_ACCESS : 0u;
-            const int32_t dt = dtr < 0 ? 0 : dtr;
-            const uint32_t ob = offv[j] & 0xFFFFu, om = offv[j] >> 16;
-            const bool one = ((e.w & 2u) != 0u) | (om == 0u);
-            const uint32_t pn = one ? 1u : (om > ob ? om - ob : 0u);
-            const uint32_t pd = one ? 1u : om;
-            // every test evaluated (no short-circuit branches)
-            const int32_t lim = ef_lim[(m >> SAE_META_NTOK_SHIFT) & 15u];
-            const bool k_ef = ((e.w & 1u) != 0u) | ((int32_t)(b0 + j) <= lim);
-            const bool k_pr = !product_prunes(pn, pd, __uint_as_float(e.y), __uint_as_float(e.z), dt);
-            const bool keep = ev & ((uint32_t)dt >= e.x) & k_pr & k_ef;
+            const bool keep = scan_keep(ent[m & 63u], m, lav[j], offv[j], b0 + j, now, ef_lim, st);
             const unsigned long long km = __ballot(keep);
-            if (keep) lst[nl + (uint32_t)__popcll(km & lt)] = make_int4(lav[j], (int32_t)offv[j], (int32_t)m, (int32_t)(b0 + j));
+            if (keep) lst[nl + (uint32_t)__popcll(km & lt)] = make_int4(lav[j], (int32_t)offv[j], (int32_t)m, b0 + j);
             nl += (uint32_t)__popcll(km);
         }
         if (nl >= SAE_WAVE) {  // wave-uniform, rare
@@ -1393,20 +1589,28 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
         }
     };
 
-    // full batches: unconditional vector loads, two batches ahead
-    for (long long bi = gw; bi < nfull; bi += 3 * tw) {  // wave-uniform
+    // unconditional vector loads, two batches ahead.  One copy of the body
+    // (the registers rotate): a wave runs few batches, so what the body costs
+    // is to a good part the fetch of its instructions
+#pragma unroll 1
+    for (int bi = gw; bi < nfull; bi += tw) {  // wave-uniform
         qc = ld(bi + 2 * tw);
         process(qa, bi);
-        if (bi + tw >= nfull) break;
-        qa = ld(bi + 3 * tw);
-        process(qb, bi + tw);
-        if (bi + 2 * tw >= nfull) break;
-        qb = ld(bi + 4 * tw);
-        process(qc, bi + 2 * tw);
+        qa = qb;
+        qb = qc;
     }
-    // the rest: per-element loads
-    for (long long bi = nfull + gw; bi < nb; bi += tw)
-        process(load_quad_safe(c, base, bi * SCAN_BATCH + lane * 4, N), bi);
+    // the arrays' last, incomplete group: its blocks are queued unfiltered (the
+    // queue has room: fewer than 64 blocks are left in it here)
+    if (qr.nvec < qr.nq && gw == 0) {  // wave-uniform
+        const int b = qr.nvec * 4 + qr.b0 + lane;
+        const bool in = lane < 4 && b >= 0 && b < N;
+        const uint32_t m = in ? (uint32_t)c.meta[base + b] : 0u;
+        const bool keep = meta_evictable(m);
+        const unsigned long long km = __ballot(keep);
+        if (keep)
+            lst[nl + (uint32_t)__popcll(km & lt)] = make_int4(c.la[base + b], (int32_t)c.off[base + b], (int32_t)m, b);
+        nl += (uint32_t)__popcll(km);
+    }
 
     // what the waves left queued, scored by the four waves together
     if (lane == 0) left_s[wave] = nl;
@@ -2190,17 +2394,29 @@ __global__ void __launch_bounds__(FIN_THREADS) k_final(DevCtx c, SelectArgs a, i
 
 // ---------------------------------------------------------------------------
 // Batched engine: one workgroup per instance (N <= 65,536 blocks).  Per
-// queue, composite e = key << 16 | id (48 bits, distinct).
-//  * The first pass reads the pool once, scores every evictable block (Eq.
-//    1-3) and caches its key and queue (5 B per block) for the later passes,
-//    counts each queue's evictable blocks and histograms the top digit of e;
-//    need = min(k, evictable).  A queue whose need is all of its blocks takes
-//    them all; otherwise the bin holding its need-th element gives a range
-//    [lo, hi) of e: every element below lo is selected, and `rem` more from
-//    inside the range.  When the range holds exactly `rem` elements, every
-//    element below hi is selected.
-//  * While the open ranges hold more elements than the candidate buffer, a
-//    pass over the cached keys histograms the next digit inside each range
+// queue, composite e = key << 16 | id (48 bits, distinct).  The selection runs
+// over a set of elements that holds every queue's k smallest, gathered in one
+// of two ways:
+//  * whole pool: every evictable block is scored (Eq. 1-3) and its key and
+//    queue cached, in LDS for a small pool (at most BATCH_LDS_N blocks), else
+//    in device memory (5 B per block);
+//  * streaming (BATCH_STREAM_N blocks and more, Q k <= BATCH_STREAM_K): the
+//    pool is read once, in rounds of 4,096 blocks, and an LDS list keeps the
+//    elements that can still be among their queue's k smallest.  After 1 and
+//    4 rounds, and whenever the list runs full, every queue's list is cut at a
+//    value that at least k of its elements do not exceed (batch_prune);
+//    from then on only blocks below it are listed, and the
+//    pool scan's exact filter (scan_keep) keeps almost all others from being
+//    scored at all.  The list always holds the first k of the blocks read so
+//    far, so the result is exact for any order of the blocks; the order only
+//    decides how many are scored.
+// A queue whose need = min(k, evictable) is all of its elements takes them
+// all; otherwise the bin holding its need-th element gives a range [lo, hi)
+// of e: every element below lo is selected, and `rem` more from inside the
+// range.  When the range holds exactly `rem` elements, every element below hi
+// is selected.
+//  * While the open ranges hold more elements than BATCH_RANK, a
+//    pass over the elements histograms the next digit inside each range
 //    (equal keys spread on the id digits).
 //  * The collect pass appends every selected element below lo to its queue's
 //    list and every element inside the range to the candidate buffer; a
@@ -2209,7 +2425,16 @@ __global__ void __launch_bounds__(FIN_THREADS) k_final(DevCtx c, SelectArgs a, i
 //  * Each queue's list (at most max_k elements) is sorted, written out, and
 //    the decision merged from the lists (Algorithm 1).
 #define BATCH_CAND 2048  // candidate elements beyond the largest lists in LDS
+#define BATCH_RANK 512   // candidates ranked by comparison (an LDS read of a wave per pair row: 1,500 took 16 us)
 #define BATCH_LQ 128     // blocks a wave's scoring list holds: < 64 left + 64 pushed
+#define BATCH_LDS_N 8192       // largest pool whose keys are cached in LDS
+#define BATCH_STREAM_N 16384   // smallest pool that is streamed
+#define BATCH_STREAM_K 4096    // largest Q k that is streamed
+#define BATCH_ROUND (4 * SEL_THREADS)             // blocks a workgroup reads per round
+#define BATCH_LIST 10240       // elements of the streaming list: a cut one (BATCH_CUT) and what each wave may
+#define BATCH_CUT 4096         //   add before it looks again (a batch of 256 blocks, 2 x 63 held back, 3 of the tail)
+static_assert(BATCH_CUT + BATCH_ROUND + 2 * SEL_THREADS <= BATCH_LIST, "a batch of every wave fits a cut list");
+static_assert(BATCH_STREAM_K <= BATCH_CUT, "a list cut exactly fits");
 #define BATCH_LQ_BYTES (SEL_THREADS / SAE_WAVE * 2 * 3 * BATCH_LQ * 4)  // the first pass's lists (48 KiB)
 struct BatchSel {
     unsigned long long lo[SAE_MAX_QUEUES], hi[SAE_MAX_QUEUES];
@@ -2218,11 +2443,19 @@ struct BatchSel {
     int32_t mode[SAE_MAX_QUEUES];  // 0: none, 1: all, 2: below lo plus rem from [lo, hi), 3: below hi
     int32_t active[SAE_MAX_QUEUES];
     int32_t sh[SAE_MAX_QUEUES], w[SAE_MAX_QUEUES];  // the next digit: bits sh .. sh + w - 1 of e
+    uint4 rng[SAE_MAX_QUEUES];  // the range for the digit passes, in one read: its prefix (x, y; none when the queue is
+                                // closed), sh | w << 8, the digit's mask
     uint32_t mn[SAE_MAX_QUEUES], mx[SAE_MAX_QUEUES];  // smallest and largest key
     Crossing cr[SAE_MAX_QUEUES];
     uint32_t seg_tot[16];
     uint32_t open_cnt, st;
     int32_t pe;
+    // streaming: the filter's tables, each queue's cut (the largest e listed) and the list's fill
+    uint4 ent[64];
+    int32_t ef_lim[16];
+    unsigned long long thr[SAE_MAX_QUEUES];
+    uint32_t fill;
+    int32_t more;  // a wave has blocks left to read
 };
 
 // A pass over the cached keys of one instance: fn(q, e) for every evictable
@@ -2280,9 +2513,20 @@ __device__ __forceinline__ void batch_cached_pass(const DevCtx &c, int inst, Fn 
     }
 }
 
+// Thread q < Q: queue q's range as the digit passes read it.  A range is an
+// aligned block of 2^(sh + w) values.
+__device__ __forceinline__ void batch_set_range(BatchSel &bs, int q)
+{
+    const int sh = bs.sh[q], w = bs.w[q];
+    const unsigned long long pre = bs.active[q] ? bs.lo[q] >> (sh + w) : ~0ull;
+    bs.rng[q] = make_uint4((uint32_t)pre, (uint32_t)(pre >> 32), (uint32_t)(sh | (w << 8)), (1u << w) - 1u);
+}
+
 // After a histogram of every open queue's digit over its range: narrow the
-// range to the crossing bin, and move to the next digit below it.
-__device__ void batch_narrow(BatchSel &bs, int Q)
+// range to the crossing bin, and move to the next digit below it.  The keys of
+// an evict-first queue are small whole numbers, so below its first digit only
+// the ids differ, and the next digit is theirs.
+__device__ void batch_narrow(BatchSel &bs, int Q, int ef)
 {
     const int tid = threadIdx.x;
     if (tid < Q && bs.active[tid]) {
@@ -2298,10 +2542,13 @@ __device__ void batch_narrow(BatchSel &bs, int Q)
             bs.active[tid] = 0;
             bs.ccnt[tid] = 0;
         } else {
-            const int w = sh < SAE_DIGIT_BITS ? sh : SAE_DIGIT_BITS;
+            const int top = (tid == ef && sh > 16 && sh <= 36) ? 16 : sh;
+            if (top != sh) bs.hi[tid] = lo + (1ull << top);
+            const int w = top < SAE_DIGIT_BITS ? top : SAE_DIGIT_BITS;
             bs.w[tid] = w;
-            bs.sh[tid] = sh - w;
+            bs.sh[tid] = top - w;
         }
+        batch_set_range(bs, tid);
     }
     lds_barrier();
     if (tid == 0) {
@@ -2312,9 +2559,320 @@ __device__ void batch_narrow(BatchSel &bs, int Q)
     lds_barrier();
 }
 
-__global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a, int P, int dyn_elems)
+// Every queue's need of the elements counted in bs.nev, and the first digit.
+__device__ void batch_start(BatchSel &bs, int Q, int kk, int top_of_all)
 {
-    extern __shared__ unsigned long long sh_dyn[];  // hist [Q][SAE_BINS] u32, later lists [Q][Pe] + candidates
+    const int tid = threadIdx.x;
+    if (tid < Q) {
+        const uint32_t need = (uint32_t)min((long long)kk, (long long)bs.nev[tid]);
+        bs.need[tid] = need;
+        bs.rem[tid] = need;
+        bs.active[tid] = 0;
+        bs.ccnt[tid] = 0;
+        if (need == 0) bs.mode[tid] = 0;
+        else if (need >= bs.nev[tid]) bs.mode[tid] = 1;
+        else {
+            // the first digit: the highest bits where the queue's keys differ
+            // (or the id bits when every key is equal), or simply the highest
+            // key bits when the extremes are not known (top_of_all)
+            const uint32_t kx = bs.mn[tid] ^ bs.mx[tid];
+            const int top = top_of_all ? top_of_all : (kx ? 16 + (32 - __clz(kx)) : 16);
+            const unsigned long long mn = top_of_all ? 0ull : (unsigned long long)bs.mn[tid] << 16;
+            const int w = top < SAE_DIGIT_BITS ? top : SAE_DIGIT_BITS;
+            bs.w[tid] = w;
+            bs.sh[tid] = top - w;
+            bs.lo[tid] = (mn >> top) << top;
+            bs.hi[tid] = bs.lo[tid] + (1ull << top);
+            bs.ccnt[tid] = bs.nev[tid];
+            bs.mode[tid] = 2;
+            bs.active[tid] = 1;
+        }
+        batch_set_range(bs, tid);
+    }
+    lds_barrier();
+    if (tid == 0) {
+        uint32_t n = 0;
+        for (int q = 0; q < Q; ++q) n += bs.active[q] ? bs.ccnt[q] : 0u;
+        bs.open_cnt = n;
+    }
+    lds_barrier();
+}
+
+// One digit of every open queue over the elements that pass(fn) visits as
+// fn(q, e), then the ranges narrowed to it.
+template <typename Pass>
+__device__ __forceinline__ void batch_digit(BatchSel &bs, int Q, int ef, uint32_t *hist, Pass pass)
+{
+    const int tid = threadIdx.x;
+    uint4 *h4 = reinterpret_cast<uint4 *>(hist);
+    for (int i = tid; i < Q * (SAE_BINS / 4); i += SEL_THREADS) h4[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < Q) bs.remv[tid] = bs.rem[tid];
+    lds_barrier();
+    pass([&](int q, unsigned long long e) {
+        const uint4 r = bs.rng[q];
+        const int sh = (int)(r.z & 0xFFu), w = (int)(r.z >> 8);
+        const unsigned long long d = e >> sh;
+        if ((d >> w) == ((unsigned long long)r.x | ((unsigned long long)r.y << 32)))
+            atomicAdd(&hist[q * SAE_BINS + ((uint32_t)d & r.w)], 1u);
+    });
+    lds_barrier();
+    find_crossing(hist, Q, bs.remv, bs.active, bs.cr, bs.seg_tot);
+    batch_narrow(bs, Q, ef);
+}
+
+#define BATCH_E48 0xFFFFFFFFFFFFull  // a list element's e; its queue is in the bits above
+
+// Cuts the streaming list: per queue a value that at least kk of its elements
+// (all of them when it has fewer) do not exceed, the list reduced to the
+// elements up to it, and the filter's tables for it.  Two digits usually cut
+// within a few per cent of the kk-th element; more are used only while the
+// list would stay longer than BATCH_CUT, and all of them cut exactly.  All
+// threads call, at a barrier.
+__device__ void batch_prune(const DevCtx &c, BatchSel &bs, const ScoreTab &tab, int Q, int kk, unsigned long long *list,
+                            uint32_t *hist)
+{
+    constexpr int PER = BATCH_LIST / SEL_THREADS;
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / SAE_WAVE;
+    const uint32_t n = bs.fill;
+    batch_start(bs, Q, kk, 47);
+    auto pass = [&](auto fn) {
+        for (uint32_t i = tid; i < n; i += SEL_THREADS) {
+            const unsigned long long x = list[i];
+            fn((int)(x >> 48), x & BATCH_E48);
+        }
+    };
+    for (int lev = 0; lev < 5 && bs.open_cnt; ++lev) {  // uniform
+        if (lev >= 2) {
+            uint32_t keep = 0;  // what the ranges' upper ends would keep
+            for (int q = 0; q < Q; ++q)
+                keep += bs.active[q] ? bs.need[q] - bs.rem[q] + bs.ccnt[q] : bs.need[q];
+            if (keep <= BATCH_CUT) break;  // uniform
+        }
+        batch_digit(bs, Q, c.ef_queue, hist, pass);
+    }
+    // no cut while a queue holds no more than kk elements (modes 0 and 1)
+    if (tid < Q) bs.thr[tid] = bs.mode[tid] <= 1 ? BATCH_E48 : bs.hi[tid] - 1ull;
+    // the elements of a thread leave the list and come back if they stay
+    unsigned long long x[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const uint32_t i = (uint32_t)(tid + u * SEL_THREADS);
+        x[u] = i < n ? list[i] : ~0ull;
+    }
+    lds_barrier();
+    if (tid == 0) {
+        bs.fill = 0;
+        bs.more = 0;
+    }
+    if (tid < SAE_MAX_QUEUES) bs.nev[tid] = 0;
+    lds_barrier();
+    uint32_t tot = 0, nq[SAE_MAX_QUEUES];  // this wave's (wave-uniform): one addition per counter and wave
+#pragma unroll
+    for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq) nq[qq] = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if ((uint32_t)(u * SEL_THREADS) < n) {  // uniform
+            const int q = (int)(x[u] >> 48) & 7;
+            if (x[u] != ~0ull && (x[u] & BATCH_E48) > bs.thr[q]) x[u] = ~0ull;
+            const bool stay = x[u] != ~0ull;
+            tot += (uint32_t)__popcll(__ballot(stay));
+#pragma unroll
+            for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq)
+                if (qq < Q) nq[qq] += (uint32_t)__popcll(__ballot(stay && q == qq));
+        }
+    }
+    uint32_t at = 0;
+    if (lane == 0 && tot) at = atomicAdd(&bs.fill, tot);
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+    for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq)
+        if (qq < Q && lane == 0 && nq[qq]) atomicAdd(&bs.nev[qq], nq[qq]);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if ((uint32_t)(u * SEL_THREADS) < n) {  // uniform
+            const unsigned long long m = __ballot(x[u] != ~0ull);
+            if (x[u] != ~0ull) list[at + (uint32_t)__popcll(m & lanemask_lt())] = x[u];
+            at += (uint32_t)__popcll(m);
+        }
+    }
+    // the filter's entries, a wave per (queue, type) in turn
+    for (int i = wave; i < Q * SAE_N_TYPES; i += SEL_THREADS / SAE_WAVE) {
+        const int q = i / SAE_N_TYPES, ty = i - q * SAE_N_TYPES;
+        const bool all = bs.thr[q] == BATCH_E48;
+        const uint32_t tk = all ? 0xFFFFFFFFu : (uint32_t)(bs.thr[q] >> 16);
+        uint32_t D = 0;
+        if (c.kind[q] == SAE_KIND_LOGNORMAL) D = lognormal_dt_floor(tab, q, ty, tk);
+        if (lane == 0) bs.ent[ty * 8 + q] = scan_entry(c.kind[q], D, tab.aw[q][ty], tk, tab.gamma);
+    }
+    if (c.ef_queue >= 0 && c.ef_queue < Q && tid < 16) {
+        const unsigned long long th = bs.thr[c.ef_queue];
+        const uint32_t tk = th == BATCH_E48 ? 0xFFFFFFFFu : (uint32_t)(th >> 16);
+        const uint32_t kb = __float_as_uint((float)(tid + 1));
+        bs.ef_lim[tid] = (kb < tk) ? 0x7FFFFFFF : ((kb == tk) ? (int32_t)(th & 0xFFFFull) : -1);
+    }
+    lds_barrier();
+}
+
+// Streams instance inst's pool into the LDS list (BatchSel::fill elements, per
+// queue BatchSel::nev).  lists: two lists of BATCH_LQ queued blocks per wave,
+// the log-normal queues' and the others' (Eq. 1 is long: a wave that held both
+// would run it for the others too).
+__device__ void batch_stream(const DevCtx &c, const SelectArgs &a, int inst, BatchSel &bs, const ScoreTab &tab, int kk,
+                             uint32_t *lists, unsigned long long *list, uint32_t *hist, uint32_t &st)
+{
+    const int Q = c.Q, N = c.N, tid = threadIdx.x, lane = lane_id(), wave = tid / SAE_WAVE;
+    constexpr int NW = SEL_THREADS / SAE_WAVE;
+    const long long base = (long long)inst * N;
+    const QuadRange qr = quad_range(c, inst);
+    const int nfull = (qr.nvec + SAE_WAVE - 1) / SAE_WAVE;
+    const int rounds = (nfull + NW - 1) / NW;
+    auto ld = [&](int bi) {
+        const int i = bi * SAE_WAVE + lane;
+        return load_quad_vec(c, qr, i < qr.nvec ? i : qr.nvec - 1);
+    };
+    Quad qa = ld(wave), qb = ld(wave + NW);
+    uint32_t *wq = lists + wave * 2 * 3 * BATCH_LQ;
+    // nothing is filtered before the first cut; queue indices >= Q select nothing
+    if (tid < 64) bs.ent[tid] = make_uint4((tid & 7) < Q ? 0u : 0xFFFFFFFFu, 0u, 0x7F800000u, 1u);
+    if (tid < 16) bs.ef_lim[tid] = 0x7FFFFFFF;
+    if (tid < SAE_MAX_QUEUES) bs.thr[tid] = BATCH_E48;
+    if (tid == 0) {
+        bs.fill = 0;
+        bs.more = 0;
+    }
+    uint32_t qm_ln = 0;  // bit q: queue q is log-normal
+    for (int qq = 0; qq < Q; ++qq) qm_ln |= (tab.kind[qq] == SAE_KIND_LOGNORMAL) ? 1u << qq : 0u;
+    lds_barrier();
+    const unsigned long long lt = lanemask_lt();
+    uint32_t n0 = 0, n1 = 0;               // fill of the two lists (wave-uniform)
+    uint32_t nq[SAE_MAX_QUEUES];           // elements this wave has listed since the last cut, per queue
+#pragma unroll
+    for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq) nq[qq] = 0;
+    // scores 64 blocks of each list that holds as many (with `all`, whatever
+    // they hold) and lists those within their queue's cut
+    auto drain = [&](bool all) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int which = 0; which < 2; ++which) {
+            uint32_t &nl = which == 0 ? n0 : n1;
+            const uint32_t n = nl >= SAE_WAVE ? (uint32_t)SAE_WAVE : (all ? nl : 0u);
+            if (n == 0) continue;  // wave-uniform
+            nl -= n;
+            const bool act = (uint32_t)lane < n;
+            const uint32_t *w = wq + which * 3 * BATCH_LQ;
+            const uint32_t p = nl + (act ? (uint32_t)lane : 0u);
+            const int32_t la = (int32_t)w[p];
+            const uint32_t off = w[BATCH_LQ + p], mb = w[2 * BATCH_LQ + p], m = mb & 0xFFFFu;
+            const int q = meta_queue(m);
+            uint32_t key;
+            if (which == 0) {
+                key = key_lognormal(a.now, la, m, tab, st);
+            } else {
+                const int kind = tab.kind[q];
+                key = key_cheap(kind, a.now, la, m, tab, st);
+                if (kind == SAE_KIND_STRUCTURAL) key = key_structural(a.now, la, m, off, tab, st);
+            }
+            const unsigned long long e = ((unsigned long long)key << 16) | (mb >> 16);
+            const bool in = act && e <= bs.thr[q];
+            const unsigned long long mk = __ballot(in);
+            if (mk == 0) continue;  // wave-uniform
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&bs.fill, (uint32_t)__popcll(mk));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(mk & lt);
+            if (in && at < BATCH_LIST) list[at] = ((unsigned long long)q << 48) | e;
+#pragma unroll
+            for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq)
+                if (qq < Q) nq[qq] += (uint32_t)__popcll(__ballot(in && q == qq));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    // queues one block per lane (b the block's id)
+    auto push = [&](bool keep, int32_t la, uint32_t off, uint32_t m, int b) {
+        const bool ln = keep && ((qm_ln >> meta_queue(m)) & 1u), other = keep && !ln;
+        const unsigned long long k0 = __ballot(ln), k1 = __ballot(other);
+        if (keep) {
+            const uint32_t p = ln ? n0 + (uint32_t)__popcll(k0 & lt) : n1 + (uint32_t)__popcll(k1 & lt);
+            uint32_t *w = wq + (ln ? 0 : 3 * BATCH_LQ);
+            w[p] = (uint32_t)la;
+            w[BATCH_LQ + p] = off;
+            w[2 * BATCH_LQ + p] = m | ((uint32_t)b << 16);
+        }
+        n0 += (uint32_t)__popcll(k0);
+        n1 += (uint32_t)__popcll(k1);
+    };
+    // A wave reads its batches until the next cut is due or the list runs full
+    // (each wave adds fewer than 384 elements between two looks at the fill),
+    // so the waves meet only at the cuts.
+    int r = 0;  // this wave's next round
+    bool tail = qr.nvec < qr.nq && wave == 0;
+#pragma unroll 1
+    for (int cut = 0;; ++cut) {
+        const int due = min(rounds, cut == 0 ? 1 : (cut == 1 ? 4 : rounds));
+#pragma unroll 1
+        while (r < due &&
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)*(volatile uint32_t *)&bs.fill) <= BATCH_CUT) {
+            const int bi = r * NW + wave;
+            const Quad qc = ld(bi + 2 * NW);
+            if (bi < nfull) {  // wave-uniform
+                const int i = bi * SAE_WAVE + lane;
+                const int b0 = i * 4 + qr.b0;
+                if (bi == 0 || bi == nfull - 1) {  // wave-uniform
+                    quad_mask(qa, b0, N);
+                    if (i >= qr.nvec) qa.m = make_uint2(0u, 0u);
+                }
+                const int32_t lav[4] = {qa.la.x, qa.la.y, qa.la.z, qa.la.w};
+                const uint32_t offv[4] = {qa.off.x, qa.off.y, qa.off.z, qa.off.w};
+                const uint32_t mv[4] = {qa.m.x & 0xFFFFu, qa.m.x >> 16, qa.m.y & 0xFFFFu, qa.m.y >> 16};
+                bool kp[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    kp[j] = scan_keep(bs.ent[mv[j] & 63u], mv[j], lav[j], offv[j], b0 + j, a.now, bs.ef_lim, st);
+#pragma unroll 1
+                for (int j = 0; j < 4; ++j) {  // one copy of the scoring code
+                    const bool keep = j == 0 ? kp[0] : (j == 1 ? kp[1] : (j == 2 ? kp[2] : kp[3]));
+                    if (!__ballot(keep)) continue;  // wave-uniform
+                    const int32_t la = j == 0 ? lav[0] : (j == 1 ? lav[1] : (j == 2 ? lav[2] : lav[3]));
+                    const uint32_t off = j == 0 ? offv[0] : (j == 1 ? offv[1] : (j == 2 ? offv[2] : offv[3]));
+                    const uint32_t m = j == 0 ? mv[0] : (j == 1 ? mv[1] : (j == 2 ? mv[2] : mv[3]));
+                    push(keep, la, off, m, b0 + j);
+                    if (n0 >= SAE_WAVE || n1 >= SAE_WAVE) drain(false);  // wave-uniform; fewer than 64 stay in each
+                }
+            }
+            qa = qb;
+            qb = qc;
+            ++r;
+        }
+        if (r >= rounds && tail) {  // wave-uniform
+            // the arrays' last, incomplete group, unfiltered
+            tail = false;
+            const int b = qr.nvec * 4 + qr.b0 + lane;
+            const bool in = lane < 4 && b >= 0 && b < N;
+            const uint32_t m = in ? (uint32_t)c.meta[base + b] : 0u;
+            const bool keep = meta_evictable(m) && meta_queue(m) < Q;
+            push(keep, keep ? c.la[base + b] : 0, keep ? c.off[base + b] : 0u, m, b);
+        }
+        // what the wave holds back (the cut's histograms take the place of its lists)
+#pragma unroll 1
+        while (n0 | n1) drain(true);  // wave-uniform
+#pragma unroll
+        for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq) {
+            if (qq < Q && lane == 0 && nq[qq]) atomicAdd(&bs.nev[qq], nq[qq]);
+            nq[qq] = 0;
+        }
+        if (r < rounds && lane == 0) bs.more = 1;
+        lds_barrier();
+        if (!bs.more) break;  // uniform: nothing writes it before the cut's first barrier
+        batch_prune(c, bs, tab, Q, kk, list, hist);
+    }
+}
+
+__global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a, int P, int dyn_elems, int list_at, int cache_at)
+{
+    // hist [Q][SAE_BINS] u32, later lists [Q][Pe] + candidates; from list_at the
+    // streaming list, from cache_at the LDS key cache (-1: none)
+    extern __shared__ unsigned long long sh_dyn[];
     uint32_t *hist = reinterpret_cast<uint32_t *>(sh_dyn);
     unsigned long long *lists = sh_dyn;
     __shared__ BatchSel bs;
@@ -2324,6 +2882,7 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     const int Q = c.Q, N = c.N;
     const int tid = threadIdx.x, lane = lane_id();
     const long long base = (long long)inst * N;
+    const int kk = inst_k(a, inst, c.max_k);
     load_score_tab(tab, c.state[inst], c);
     if (tid < SAE_MAX_QUEUES) {
         bs.nev[tid] = 0;
@@ -2337,6 +2896,17 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     if (tid == 0) bs.st = 0;
     lds_barrier();
 
+    uint32_t st = 0;
+    // the streaming path needs its lists (Q x pow2(kk)) and candidates before its list
+    const bool stream = list_at >= 0 && Q * kk <= BATCH_STREAM_K && kk > 0 &&
+                        Q * pow2_ge(kk) + BATCH_CAND <= list_at;  // uniform
+    unsigned long long *slist = sh_dyn + (list_at >= 0 ? list_at : 0);
+    uint32_t *ckey = reinterpret_cast<uint32_t *>(sh_dyn + (cache_at >= 0 ? cache_at : 0));
+    uint8_t *cq = reinterpret_cast<uint8_t *>(ckey + N);
+    if (stream) {
+        batch_stream(c, a, inst, bs, tab, kk, hist, slist, hist, st);
+        batch_start(bs, Q, kk, 47);
+    } else {
     // first pass: score, cache, count, smallest and largest key per queue
     uint32_t cnt_r[SAE_MAX_QUEUES], mn_r[SAE_MAX_QUEUES], mx_r[SAE_MAX_QUEUES];
 #pragma unroll
@@ -2345,7 +2915,6 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
         mn_r[q] = 0xFFFFFFFFu;
         mx_r[q] = 0;
     }
-    uint32_t st = 0;
     {
         // A wave's lanes hold blocks of every queue kind, and Eq. 1 (ln,
         // erfc) and Eq. 2 are long: scored in place, every wave would run
@@ -2377,8 +2946,13 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
                     mx_r[qq] = (qq == q) ? max(mx_r[qq], key) : mx_r[qq];
                 }
             }
-            c.bkey[base + b] = key;
-            c.bq[base + b] = ev ? (uint8_t)(q + 1) : (uint8_t)0;
+            if (cache_at >= 0) {  // uniform
+                ckey[b] = key;
+                cq[b] = ev ? (uint8_t)(q + 1) : (uint8_t)0;
+            } else {
+                c.bkey[base + b] = key;
+                c.bq[base + b] = ev ? (uint8_t)(q + 1) : (uint8_t)0;
+            }
         };
         // Score the lists: each one that holds 64 (or, at the end, whatever
         // it holds).  One call site, so that the two long key functions are
@@ -2462,12 +3036,8 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     }
 #pragma unroll
     for (int q = 0; q < SAE_MAX_QUEUES; ++q) {
-        uint32_t v = cnt_r[q], lo = mn_r[q], hi = mx_r[q];
-        for (int o = 32; o > 0; o >>= 1) {
-            v += __shfl_xor(v, o, SAE_WAVE);
-            lo = min(lo, (uint32_t)__shfl_xor(lo, o, SAE_WAVE));
-            hi = max(hi, (uint32_t)__shfl_xor(hi, o, SAE_WAVE));
-        }
+        if (q >= Q) break;  // uniform
+        const uint32_t v = wave_sum(cnt_r[q]), lo = wave_min(mn_r[q]), hi = wave_max(mx_r[q]);
         if (lane == 0 && v) {
             atomicAdd(&bs.nev[q], v);
             atomicMin(&bs.mn[q], lo);
@@ -2475,62 +3045,40 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
         }
     }
     lds_barrier();
-    if (tid < Q) {
-        const int kk = inst_k(a, inst, c.max_k);
-        const uint32_t need = (uint32_t)min((long long)kk, (long long)bs.nev[tid]);
-        bs.need[tid] = need;
-        bs.rem[tid] = need;
-        if (need == 0) bs.mode[tid] = 0;
-        else if (need >= bs.nev[tid]) bs.mode[tid] = 1;
-        else {
-            // the first digit: the highest bits where the queue's keys differ,
-            // or the id bits when every key is equal
-            const uint32_t kx = bs.mn[tid] ^ bs.mx[tid];
-            const int top = kx ? 16 + (32 - __clz(kx)) : 16;  // bits of e below the common prefix
-            const unsigned long long mn = (unsigned long long)bs.mn[tid] << 16;
-            const int w = top < SAE_DIGIT_BITS ? top : SAE_DIGIT_BITS;
-            bs.w[tid] = w;
-            bs.sh[tid] = top - w;
-            bs.lo[tid] = (mn >> top) << top;
-            bs.hi[tid] = bs.lo[tid] + (1ull << top);
-            bs.ccnt[tid] = bs.nev[tid];
-            bs.mode[tid] = 2;
-            bs.active[tid] = 1;
-        }
+    batch_start(bs, Q, kk, 0);
     }
-    lds_barrier();
     if (tid == 0) {  // list segments of Pe = pow2 >= the largest need
         uint32_t mx = 1;
         for (int q = 0; q < Q; ++q) mx = bs.need[q] > mx ? bs.need[q] : mx;
         bs.pe = pow2_ge((int)mx) < P ? pow2_ge((int)mx) : P;
     }
     lds_barrier();
-    if (tid == 0) {
-        uint32_t n = 0;
-        for (int q = 0; q < Q; ++q) n += bs.active[q] ? bs.ccnt[q] : 0u;
-        bs.open_cnt = n;
-    }
     const int Pe = bs.pe;
     // the lists take Q x Pe elements at the start of the dynamic LDS, the
     // candidates follow (ranked by comparison, so their number is bounded)
     unsigned long long *cand = sh_dyn + (long long)Q * Pe;
     // every thread's cached keys are visible to the whole workgroup from here
     __syncthreads();
-    // digit passes over the cached keys while the open ranges hold more than
-    // the candidate buffer (each narrows every open range by up to 11 bits;
-    // 48-bit composites need at most 5)
-    for (int lev = 0; lev < 5 && bs.open_cnt > BATCH_CAND; ++lev) {  // uniform
-        for (int i = tid; i < Q * SAE_BINS; i += blockDim.x) hist[i] = 0;
-        if (tid < Q) bs.remv[tid] = bs.rem[tid];
-        lds_barrier();
-        batch_cached_pass(c, inst, [&](int q, unsigned long long e) {
-            if (bs.active[q] && e >= bs.lo[q] && e < bs.hi[q])
-                atomicAdd(&hist[q * SAE_BINS + ((uint32_t)(e >> bs.sh[q]) & ((1u << bs.w[q]) - 1u))], 1u);
-        });
-        lds_barrier();
-        find_crossing(hist, Q, bs.remv, bs.active, bs.cr, bs.seg_tot);
-        batch_narrow(bs, Q);
-    }
+    const uint32_t sn = bs.fill;
+    auto pass = [&](auto fn) {  // fn(q, e) for every element
+        if (stream) {
+            for (uint32_t i = tid; i < sn; i += SEL_THREADS) {
+                const unsigned long long x = slist[i];
+                fn((int)(x >> 48), x & BATCH_E48);
+            }
+        } else if (cache_at >= 0) {
+            for (int b = tid; b < N; b += SEL_THREADS) {
+                const uint32_t qb = cq[b];
+                if (qb) fn((int)qb - 1, ((unsigned long long)ckey[b] << 16) | (uint32_t)b);
+            }
+        } else {
+            batch_cached_pass(c, inst, fn);
+        }
+    };
+    // digit passes while the open ranges hold more than is ranked by comparison
+    // (each narrows every open range by up to 11 bits; 48-bit composites need
+    // at most 5)
+    for (int lev = 0; lev < 5 && bs.open_cnt > BATCH_RANK; ++lev) batch_digit(bs, Q, c.ef_queue, hist, pass);  // uniform
     // candidates per open queue
     if (tid == 0) {
         uint32_t o = 0;
@@ -2543,7 +3091,7 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     if (tid < Q) bs.ccnt[tid] = 0;  // from here the fill count of the queue's candidates
     lds_barrier();
     // collect
-    batch_cached_pass(c, inst, [&](int q, unsigned long long e) {
+    pass([&](int q, unsigned long long e) {
         const int md = bs.mode[q];
         const bool sel = md == 1 || (md == 3 && e < bs.hi[q]) || (md == 2 && e < bs.lo[q]);
         const unsigned long long v = ((e >> 16) << 32) | (e & 0xFFFFull);
@@ -2568,7 +3116,8 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     }
     if (st) atomicOr(&bs.st, st);
     lds_barrier();
-    if (Pe >= 256 && 2 * Q * Pe <= dyn_elems) sort_segments_lds(lists, Q * Pe, Pe);
+    if (Q * Pe <= 4 * SEL_THREADS) sort_segments_rank(lists, Q * Pe, Pe);
+    else if (Pe >= 256 && 2 * Q * Pe <= dyn_elems) sort_segments_lds(lists, Q * Pe, Pe);
     else bitonic_sort_segments(lists, Q, Pe, Pe);
     if (tid < Q) cnt_s[tid] = (int32_t)min(bs.need[tid], (uint32_t)P);
     lds_barrier();
@@ -2585,8 +3134,7 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
         a.count[(long long)inst * Q + tid] = cnt_s[tid];
         c.sel_count[(long long)inst * Q + tid] = cnt_s[tid];
     }
-    const int kk = inst_k(a, inst, c.max_k);
-    const int d = merge_decision(lists, Pe, cnt_s, Q, c.ef_queue, kk, a.decision + (long long)inst * c.max_k);
+    const int d = merge_decision_lds(lists, Pe, cnt_s, Q, c.ef_queue, kk, a.decision + (long long)inst * c.max_k);
     if (tid == 0) {
         a.decision_count[inst] = d;
         if (!(a.flags & SAE_SS_CASCADE)) commit_bookkeeping(c.state[inst], d, (a.flags & SAE_SS_COMMIT) != 0);
@@ -3037,10 +3585,20 @@ hipError_t launch_select_batched(const DevCtx &c, const SelectArgs &a, hipStream
     const size_t h = (size_t)c.Q * SAE_BINS * 4, l = ((size_t)c.Q * P + BATCH_CAND) * 8;
     size_t lds = h > l ? h : l;
     if (lds < (size_t)BATCH_LQ_BYTES) lds = BATCH_LQ_BYTES;  // the first pass's scoring lists
+    // a large pool adds the streaming list, a small one the key cache, where they fit
+    int list_at = -1, cache_at = -1;
+    const size_t most = 156 * 1024;  // of the 160 KiB, the rest for the static part
+    if (c.N >= BATCH_STREAM_N && lds + (size_t)BATCH_LIST * 8 <= most) {
+        list_at = (int)(lds / 8);
+        lds += (size_t)BATCH_LIST * 8;
+    } else if (c.N <= BATCH_LDS_N && lds + (size_t)c.N * 5 <= most) {
+        cache_at = (int)(lds / 8);
+        lds += ((size_t)c.N * 5 + 15) / 16 * 16;
+    }
     const int dyn_elems = (int)(lds / 8);
     hipError_t e = allow_lds((const void *)k_batched, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_batched, dim3(c.n_inst), dim3(SEL_THREADS), lds, s, c, a, P, dyn_elems);
+    hipLaunchKernelGGL(k_batched, dim3(c.n_inst), dim3(SEL_THREADS), lds, s, c, a, P, dyn_elems, list_at, cache_at);
     return hipGetLastError();
 }
 

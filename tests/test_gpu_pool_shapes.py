@@ -82,3 +82,56 @@ def test_largest_k_without_fallback():
         assert not p.status()
     finally:
         p.close()
+
+
+def newest_last(pool, rng):
+    """Every block older than the ones before it: each one is among the k smallest so far."""
+    pool["last_access"] = np.sort(pool["last_access"])[::-1].copy()
+
+
+def newest_first(pool, rng):
+    pool["last_access"] = np.sort(pool["last_access"])
+
+
+def clusters(pool, rng):
+    pool["last_access"] = (synth.pools.NOW - 1000 * rng.integers(1, 13, pool["n_blocks"])).astype(np.int32)
+
+
+def late_queue(pool, rng):
+    """Queue 2 only in the last tenth of the pool, the evict-first queue only in the first blocks."""
+    n, q = pool["n_blocks"], pool["queue"]
+    q[: n - n // 10][q[: n - n // 10] == 2] = 3
+    q[64:][q[64:] == 0] = 4
+
+
+def edges(pool, rng):
+    """Blocks accessed now and in the future, partly filled blocks, offsets at their ends."""
+    n = pool["n_blocks"]
+    pool["last_access"][rng.random(n) < 0.3] = synth.pools.NOW
+    pool["last_access"][rng.random(n) < 0.05] = synth.pools.NOW + 5
+    pool["ntok"] = rng.integers(1, 17, n).astype(np.int32)
+    pool["ob"] = np.where(rng.random(n) < 0.5, pool["omax"], 0).astype(np.int32)
+
+
+# the streaming path of the batched engine: from 16,384 blocks on and Q k <= 4,096, several cuts, every alignment
+@pytest.mark.parametrize("N,k", [(16384, 1), (16385, 64), (16387, 819), (16383, 64), (40001, 819), (65535, 257),
+                                 (65536, 256), (65536, 820)])
+def test_batched_streaming_sizes(N, k):
+    say("batched: 3 instances of %d blocks, k %d" % (N, k))
+    assert several(3, N, k, api.SS_ENGINE_BATCHED) == []
+
+
+@pytest.mark.parametrize("edit", [newest_last, newest_first, clusters, late_queue, edges])
+def test_batched_streaming_orders(edit):
+    say("batched: %s" % edit.__name__)
+    st = several(3, 30003, 300, api.SS_ENGINE_BATCHED, edit=edit, k_per=[300, 0, 7])
+    assert set(st) <= {"FUTURE_ACCESS"}
+    say("scan: %s" % edit.__name__)
+    several(3, 30003, 300, api.SS_ENGINE_SCAN, edit=edit, k_per=[300, 0, 7])
+
+
+# one wave, one workgroup round, the LDS key cache's limit and the sorts' segment sizes
+@pytest.mark.parametrize("N,k", [(1, 1), (63, 2), (1024, 128), (1025, 129), (8192, 256), (8193, 100), (9001, 1)])
+def test_batched_small_pools(N, k):
+    say("batched: 4 instances of %d blocks, k %d" % (N, k))
+    several(4, N, k, api.SS_ENGINE_BATCHED)
