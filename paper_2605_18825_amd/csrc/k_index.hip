@@ -22,87 +22,43 @@ namespace {
 constexpr int kThreads = 256;
 
 __device__ __forceinline__ bool index_insert(IndexSlot *tab, uint32_t mask, unsigned long long h, int32_t id,
-                                             uint32_t tq)
+                                             uint32_t tq, int p = 0)
 {
-    uint32_t s = hash_home(h, mask);
-    for (int p = 0; p <= (int)mask && p < SAE_MAX_PROBES; ++p) {
-        unsigned long long v = tab[s].hash;
-        if (v == SAE_EMPTY_HASH || v == SAE_TOMB_HASH) {
-            unsigned long long old = atomicCAS(&tab[s].hash, v, h);
-            if (old == v) {
-                *reinterpret_cast<uint2 *>(&tab[s].id) = make_uint2((uint32_t)id, tq);
-                return true;
-            }
-            continue;  // lost the slot: look at it again
-        }
-        s = (s + 1) & mask;
-    }
-    return false;
-}
-
-// index_insert with the home slot's hash already loaded, and the lookup of a
-// live, unconsumed recently_evicted entry of hash h (its table slot index, or
-// -1; *ring_pos its ring position) likewise.
-__device__ __forceinline__ bool index_insert_from(IndexSlot *tab, uint32_t mask, unsigned long long h, int32_t id,
-                                                  uint32_t tq, uint32_t s0, unsigned long long v0)
-{
-    uint32_t s = s0;
-    unsigned long long v = v0;
-    bool fresh = true;  // v holds slot s's hash as loaded
-    for (int p = 0; p <= (int)mask && p < SAE_MAX_PROBES; ++p) {
-        if (!fresh) v = tab[s].hash;
-        fresh = false;
-        if (v == SAE_EMPTY_HASH || v == SAE_TOMB_HASH) {
-            const unsigned long long old = atomicCAS(&tab[s].hash, v, h);
-            if (old == v) {
-                *reinterpret_cast<uint2 *>(&tab[s].id) = make_uint2((uint32_t)id, tq);
-                return true;
-            }
-            continue;  // lost the slot: look at it again
-        }
-        s = (s + 1) & mask;
-    }
-    return false;
-}
-
-__device__ __forceinline__ int ghost_find_from(const GhostSlot *tab, uint32_t mask, const GhostEntry *ring,
-                                               unsigned long long h, long long ev_now, int W, uint32_t s0,
-                                               unsigned long long v0, uint32_t *ring_pos)
-{
-    if (SAE_HASH_RESERVED(h)) return -1;
-    uint32_t s = s0;
-    for (int p = 0; p <= (int)mask && p < SAE_MAX_PROBES; ++p) {
-        const unsigned long long v = p == 0 ? v0 : tab[s].hash;
-        if (v == SAE_EMPTY_HASH) return -1;
-        if (v == h) {
-            const uint32_t r = tab[s].ring;
-            const GhostEntry &g = ring[r];
-            if (g.hash == h && !(g.tq & SAE_TQ_CONSUMED) && ev_now - g.stamp < (long long)W) {
-                *ring_pos = r;
-                return (int)s;
-            }
-        }
-        s = (s + 1) & mask;
-    }
-    return -1;
+    const long long s = probe_claim(tab, mask, h, p);
+    if (s >= 0) *reinterpret_cast<uint2 *>(&tab[s].id) = make_uint2((uint32_t)id, tq);
+    return s >= 0;
 }
 
 __device__ __forceinline__ bool ghost_insert(GhostSlot *tab, uint32_t mask, unsigned long long h, uint32_t ring_pos)
 {
-    uint32_t s = hash_home(h, mask);
-    for (int p = 0; p <= (int)mask && p < SAE_MAX_PROBES; ++p) {
-        unsigned long long v = tab[s].hash;
-        if (v == SAE_EMPTY_HASH || v == SAE_TOMB_HASH) {
-            unsigned long long old = atomicCAS(&tab[s].hash, v, h);
-            if (old == v) {
-                tab[s].ring = ring_pos;
-                return true;
-            }
-            continue;
-        }
-        s = (s + 1) & mask;
+    const long long s = probe_claim(tab, mask, h, 0);
+    if (s >= 0) tab[s].ring = ring_pos;
+    return s >= 0;
+}
+
+__device__ __forceinline__ bool ghost_live(const GhostEntry &g, unsigned long long h, long long ev_now, int W)
+{
+    return g.hash == h && !(g.tq & SAE_TQ_CONSUMED) && ev_now - g.stamp < (long long)W;
+}
+
+// The ring position of the live, unconsumed recently_evicted entry of h, from
+// the p-th slot of its probe sequence on, or -1.
+__device__ __forceinline__ long long ghost_find(const GhostSlot *tab, uint32_t mask, const GhostEntry *ring,
+                                                unsigned long long h, long long ev_now, int W, int p)
+{
+    const uint32_t home = hash_home(h, mask);
+    const int lim = probe_limit(mask);
+    while (p < lim) {
+        bool end;
+        const int at = probe_hash(probe_load(tab, mask, home + (uint32_t)p), h, &end);
+        p += at;
+        if (at == PROBE_G) continue;
+        if (end || p >= lim) return -1;
+        const uint32_t r = tab[(home + (uint32_t)p) & mask].ring;
+        if (ghost_live(ring[r], h, ev_now, W)) return (long long)r;
+        ++p;
     }
-    return false;
+    return -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -252,8 +208,15 @@ __global__ void k_insert_a(DevCtx c, int n, const int32_t *inst_a, const int32_t
     int32_t b = ids[i];
     const unsigned long long h = hash[i];
     const bool ok = inst >= 0 && inst < c.n_inst && b >= 0 && b < c.N;
-    // the slot's meta and the first probes of the index and of recently_evicted
-    // go out together (addresses clamped into the instance's tables)
+    // Four round trips: the row; the slot's meta, the instance's scalars and
+    // the first probes of both tables (addresses clamped into the instance's
+    // tables); the index slot's compare-and-swap with the recently_evicted
+    // entry; that entry's consumption.  The plain stores go out after the last
+    // load that is waited for, as a wait for a load also waits for the stores
+    // issued before it.
+    const uint32_t m = meta[i] & (0x7u | (0x7u << 3) | (0xFu << 9));
+    const int32_t la_i = la[i], parent_i = parent[i];
+    const uint32_t off_i = off[i];
     const int ic = ok ? inst : 0;
     const long long g = (long long)ic * c.N + (ok ? b : 0);
     IndexSlot *tab = c.index + (long long)ic * ((long long)c.index_mask + 1);
@@ -261,7 +224,9 @@ __global__ void k_insert_a(DevCtx c, int n, const int32_t *inst_a, const int32_t
     GhostEntry *ring = c.ring + (long long)ic * c.ring_cap;
     const uint32_t si = hash_home(h, c.index_mask), sg = hash_home(h, c.ghost_mask);
     const uint32_t mg = c.meta[g];
-    const unsigned long long vi = tab[si].hash, vg = gt[sg].hash;
+    const uint32_t learn = c.state[ic].learn;
+    const long long ev_now = c.state[ic].ev_count;
+    const ProbeGroup vi = probe_load(tab, c.index_mask, si), vg = probe_load(gt, c.ghost_mask, sg);
     if (!ok) {
         skip[i] = 1;
         set_status(c.status, SAE_ST_BAD_BLOCK);
@@ -277,32 +242,40 @@ __global__ void k_insert_a(DevCtx c, int n, const int32_t *inst_a, const int32_t
         set_status(c.status, SAE_ST_SLOT_BUSY);
         return;
     }
-    skip[i] = 0;
-    uint32_t m = meta[i] & (0x7u | (0x7u << 3) | (0xFu << 9));
-    c.meta[g] = (uint16_t)(m | SAE_META_VALID | SAE_META_LEAF);
-    c.la[g] = la[i];
-    c.off[g] = off[i];
-    c.hash[g] = h;
-    c.parent[g] = parent[i];
-    c.child_count[g] = 0;
-    c.ref_count[g] = 0;
-    c.access_count[g] = 0;
-    if (!index_insert_from(tab, c.index_mask, h, b, slot_tq(m, off[i]), si, vi))
-        set_status(c.status, SAE_ST_INDEX_FULL);
-    int32_t *cs = counter_slot(c, inst, i);
-    atomicAdd(cs + SAE_CF_RES + meta_queue(m), 1);
-    if (c.state[inst].learn & SAE_LEARN_TOKEN_EMA) atomicAdd(cs + SAE_CF_TADD + meta_type(m) % SAE_N_TYPES, 1);
+    bool none;
+    unsigned long long vf;
+    const int ti = probe_free(vi, &vf), tg = probe_hash(vg, h, &none);
+    const uint32_t sf = (si + (uint32_t)ti) & c.index_mask;
     // recently_evicted: a hit counts one miss after eviction (Algorithm 1,
     // Add) and consumes the entry; its table slot then stays stale (a lookup
     // skips a consumed entry) until the table is rebuilt from the ring
-    uint32_t rp = 0;
-    if (ghost_find_from(gt, c.ghost_mask, ring, h, c.state[inst].ev_count, c.W, sg, vg, &rp) >= 0) {
-        const uint32_t old = atomicOr(&ring[rp].tq, SAE_TQ_CONSUMED);
-        if (!(old & SAE_TQ_CONSUMED)) {
-            atomicAdd(cs + SAE_CF_MISSED + (old & 7u) % SAE_N_TYPES, 1);
-            if (((c.struct_mask >> ((old >> 3) & 7u)) & 1u) && (c.state[inst].learn & SAE_LEARN_DECAY_POWER))
-                atomicAdd(cs + SAE_CF_BMISS + ((old >> SAE_TQ_BIN_SHIFT) & (SAE_N_BINS - 1)), 1);
-        }
+    long long rp = -1;
+    const bool held = tg < PROBE_G && !none;
+    if (held) rp = (long long)gt[(sg + (uint32_t)tg) & c.ghost_mask].ring;
+    unsigned long long oi = ~vf;
+    if (ti < PROBE_G) oi = atomicCAS(&tab[sf].hash, vf, h);
+    if (held && !ghost_live(ring[rp], h, ev_now, c.W)) rp = ghost_find(gt, c.ghost_mask, ring, h, ev_now, c.W, tg + 1);
+    if (tg == PROBE_G) rp = ghost_find(gt, c.ghost_mask, ring, h, ev_now, c.W, PROBE_G);
+    const uint32_t old = rp >= 0 ? atomicOr(&ring[rp].tq, SAE_TQ_CONSUMED) : SAE_TQ_CONSUMED;
+    skip[i] = 0;
+    c.meta[g] = (uint16_t)(m | SAE_META_VALID | SAE_META_LEAF);
+    c.la[g] = la_i;
+    c.off[g] = off_i;
+    c.hash[g] = h;
+    c.parent[g] = parent_i;
+    c.child_count[g] = 0;
+    c.ref_count[g] = 0;
+    c.access_count[g] = 0;
+    int32_t *cs = counter_slot(c, inst, i);
+    atomicAdd(cs + SAE_CF_RES + meta_queue(m), 1);
+    if (learn & SAE_LEARN_TOKEN_EMA) atomicAdd(cs + SAE_CF_TADD + meta_type(m) % SAE_N_TYPES, 1);
+    const uint32_t tq = slot_tq(m, off_i);
+    if (oi == vf) *reinterpret_cast<uint2 *>(&tab[sf].id) = make_uint2((uint32_t)b, tq);
+    else if (!index_insert(tab, c.index_mask, h, b, tq, ti)) set_status(c.status, SAE_ST_INDEX_FULL);
+    if (!(old & SAE_TQ_CONSUMED)) {
+        atomicAdd(cs + SAE_CF_MISSED + (old & 7u) % SAE_N_TYPES, 1);
+        if (((c.struct_mask >> ((old >> 3) & 7u)) & 1u) && (learn & SAE_LEARN_DECAY_POWER))
+            atomicAdd(cs + SAE_CF_BMISS + ((old >> SAE_TQ_BIN_SHIFT) & (SAE_N_BINS - 1)), 1);
     }
 }
 
