@@ -130,6 +130,18 @@ def test_batched_streaming_orders(edit):
     several(3, 30003, 300, api.SS_ENGINE_SCAN, edit=edit, k_per=[300, 0, 7])
 
 
+# equal keys in clusters: ranked by comparison, refined by a wave (from 65) or by the workgroup (from 513)
+@pytest.mark.parametrize("size", [64, 65, 130, 512, 513, 1500])
+def test_scan_clusters_of_equal_keys(size):
+    def same_time(pool, rng):
+        n = pool["n_blocks"]
+        g = rng.permutation(n) // (4 * size)  # about `size` of them in each of the larger queues
+        pool["last_access"] = (synth.pools.NOW - 50 * (1 + g)).astype(np.int32)
+
+    say("scan: clusters of %d" % size)
+    several(2, 40009, 3000, api.SS_ENGINE_SCAN, edit=same_time)
+
+
 # one wave, one workgroup round, the LDS key cache's limit and the sorts' segment sizes
 @pytest.mark.parametrize("N,k", [(1, 1), (63, 2), (1024, 128), (1025, 129), (8192, 256), (8193, 100), (9001, 1)])
 def test_batched_small_pools(N, k):
