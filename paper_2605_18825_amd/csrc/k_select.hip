@@ -1074,6 +1074,7 @@ __device__ uint32_t lognormal_dt_floor(const ScoreTab &t, int q, int ty, uint32_
 // spread subset -- and the last one is the bound.  Also writes the scan's
 // filter entries and empties the queue's candidate stripes.
 #define ALL_EST 2048.0
+#define FIN_G 16  // buckets a workgroup of the ranking takes
 static_assert(SAMPLE_WGS <= SAE_WAVE, "the chunks' counts fit one wave");
 static_assert(SAMPLE_WGS * SAMPLE_CHUNK <= LCAP, "a queue's sampled elements fit the LDS staging area");
 struct SplitShared {
@@ -1124,7 +1125,8 @@ __device__ void split_queue(const DevCtx &c, const SelectArgs &a, int q, int ins
         if (tid == SAMPLE_WGS - 1) cpre[SAMPLE_WGS] = inc;
     }
     // this call's candidate stripes start empty
-    if (tid <= SAE_STRIPES) c.stripe_n[iq * (SAE_STRIPES + 1) + tid] = 0;
+    static_assert(SAE_CELLS < SEL_THREADS, "one thread per counter");
+    if (tid <= SAE_CELLS) c.stripe_n[iq * (SAE_CELLS + 1) + tid] = 0;
     if (tid == SEL_THREADS - 1) {
         nsp_s = 0;
         nb_s = 0;
@@ -1239,6 +1241,12 @@ __device__ void split_queue(const DevCtx &c, const SelectArgs &a, int q, int ins
     lds_barrier();
     const int nb = nb_s;
     if (tid < nb) c.split[iq * SAE_NBUCKET + tid] = spl[tid];
+    // the candidate ranges: a quarter of the buckets each, cut between the
+    // ranking's workgroups (any ascending ends are valid)
+    if (tid < SAE_PARTS) {
+        const int b = (nb * (tid + 1) / SAE_PARTS + FIN_G / 2) / FIN_G * FIN_G;
+        c.cend[iq * SAE_PARTS + tid] = (tid == SAE_PARTS - 1 || b >= nb) ? ~0ull : (b > 0 ? spl[b - 1] : 0ull);
+    }
     if (tid == 0) {
         c.thr[iq] = bound_s;
         c.nsplit[iq] = nb;
@@ -1476,8 +1484,11 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
     __shared__ uint32_t left_s[SCAN_WAVES + 1];
     __shared__ int4 s_lst[SCAN_WAVES][SCAN_LIST];  // queued blocks: last_access, off, meta, id
     __shared__ unsigned long long cbuf[SAE_MAX_QUEUES][SCAN_CB];  // this workgroup's candidates per queue
-    __shared__ uint32_t res_base[SAE_MAX_QUEUES], res_n[SAE_MAX_QUEUES], ovf_base[SAE_MAX_QUEUES],
-        ovf_n[SAE_MAX_QUEUES];
+    // per queue and range: upper end, candidates, first slot in the stripe and,
+    // past its capacity, in the overflow list
+    __shared__ unsigned long long cend_s[SAE_MAX_QUEUES * SAE_PARTS];
+    __shared__ uint32_t res_n[SAE_MAX_QUEUES * SAE_PARTS], res_base[SAE_MAX_QUEUES * SAE_PARTS],
+        ovf_base[SAE_MAX_QUEUES * SAE_PARTS];
     const int inst = blockIdx.y;
     const int wg = blockIdx.x;
     const int Q = c.Q;
@@ -1508,13 +1519,19 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
         thr_s[q] = (q < Q) ? c.thr[(long long)inst * Q + q] : 0ull;
         cnt_s[q] = 0;
     }
+    if (tid >= 192 && tid < 192 + SAE_MAX_QUEUES * SAE_PARTS) {
+        const int i = tid - 192;
+        cend_s[i] = i < Q * SAE_PARTS ? c.cend[(long long)inst * Q * SAE_PARTS + i] : 0ull;
+        res_n[i] = 0;
+    }
+    static_assert(192 + SAE_MAX_QUEUES * SAE_PARTS <= SCAN_THREADS, "one thread per range");
     if (tid == 0) st_s = 0;
     __syncthreads();
 
     const int now = a.now;
     uint32_t st = 0;
     unsigned long long *cand = c.cand + (long long)inst * Q * 2 * SAE_LCAP;
-    uint32_t *stripe_n = c.stripe_n + (long long)inst * Q * (SAE_STRIPES + 1);
+    uint32_t *stripe_n = c.stripe_n + (long long)inst * Q * (SAE_CELLS + 1);
     int4 *lst = s_lst[wave];
 
     // append (key, id) of an evictable block if it is within its queue's bound:
@@ -1538,7 +1555,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
             if (ms) {
                 const int ls = __ffsll((long long)ms) - 1;
                 uint32_t sb = 0;
-                if (lane == ls) sb = atomicAdd(&stripe_n[qq * (SAE_STRIPES + 1) + SAE_STRIPES], (uint32_t)__popcll(ms));
+                if (lane == ls) sb = atomicAdd(&stripe_n[qq * (SAE_CELLS + 1) + SAE_CELLS], (uint32_t)__popcll(ms));
                 sb = __shfl(sb, ls, SAE_WAVE);
                 if (in_e && pos >= SCAN_CB) {
                     const uint32_t sp = sb + (uint32_t)__popcll(ms & lanemask_lt());
@@ -1636,31 +1653,51 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
     if (st) atomicOr(&st_s, st);
     lds_barrier();
     // the buffered candidates go to stripe wg mod SAE_STRIPES of their queue
-    // (one reservation per queue), the part that does not fit it to the
-    // queue's overflow list (a second reservation, rarely); then every thread
-    // stores
+    // and range (one reservation each), what does not fit it to the queue's
+    // overflow list (a second reservation, rarely); then every thread stores
+    constexpr int PUT = SAE_MAX_QUEUES * SCAN_CB / SCAN_THREADS;
+    static_assert(PUT * SCAN_THREADS == SAE_MAX_QUEUES * SCAN_CB, "a thread's share of the buffers");
+    uint32_t cell[PUT], pos[PUT];  // queue and range, position among this workgroup's; cell ~0: none
+#pragma unroll
+    for (int u = 0; u < PUT; ++u) {
+        const int i = tid + u * SCAN_THREADS, q = i / SCAN_CB;
+        cell[u] = ~0u;
+        pos[u] = 0;
+        if ((uint32_t)(i % SCAN_CB) < min(cnt_s[q], (uint32_t)SCAN_CB)) {
+            const unsigned long long e = cbuf[q][i % SCAN_CB];
+            uint32_t p = 0;
+#pragma unroll
+            for (int t = 0; t < SAE_PARTS - 1; ++t) p += e > cend_s[q * SAE_PARTS + t] ? 1u : 0u;
+            cell[u] = (uint32_t)q * SAE_PARTS + p;
+            pos[u] = atomicAdd(&res_n[cell[u]], 1u);
+        }
+    }
+    lds_barrier();
     const uint32_t stripe = (uint32_t)wg % SAE_STRIPES;
-    if (tid < Q) {
-        const uint32_t n = min(cnt_s[tid], (uint32_t)SCAN_CB);
-        const uint32_t b = n ? atomicAdd(&stripe_n[tid * (SAE_STRIPES + 1) + stripe], n) : 0u;
+    if (tid < Q * SAE_PARTS) {
+        const int q = tid / SAE_PARTS, p = tid % SAE_PARTS;
+        const uint32_t n = res_n[tid];
+        uint32_t *sn = stripe_n + q * (SAE_CELLS + 1);
+        const uint32_t b = n ? atomicAdd(&sn[p * SAE_STRIPES + stripe], n) : 0u;
         const uint32_t fit = b >= SAE_STRIPE_CAP ? 0u : min(n, (uint32_t)SAE_STRIPE_CAP - b);
-        res_n[tid] = n;
         res_base[tid] = b;
-        ovf_n[tid] = fit;  // buffered candidates that fit the stripe
-        ovf_base[tid] = (n > fit) ? atomicAdd(&stripe_n[tid * (SAE_STRIPES + 1) + SAE_STRIPES], n - fit) : 0u;
+        res_n[tid] = fit;  // from here those that fit the stripe
+        ovf_base[tid] = (n > fit) ? atomicAdd(&sn[SAE_CELLS], n - fit) : 0u;
     }
     if (tid == 0) set_status(c.status, st_s);
     lds_barrier();
-    for (int i = tid; i < Q * SCAN_CB; i += SCAN_THREADS) {
-        const int q = i / SCAN_CB;
-        const uint32_t j = (uint32_t)(i - q * SCAN_CB);
-        if (j >= res_n[q]) continue;
+#pragma unroll
+    for (int u = 0; u < PUT; ++u) {
+        if (cell[u] == ~0u) continue;
+        const int i = tid + u * SCAN_THREADS, q = i / SCAN_CB;
         unsigned long long *cq = cand + (long long)q * 2 * SAE_LCAP;
-        if (j < ovf_n[q]) {
-            cq[stripe * SAE_STRIPE_CAP + res_base[q] + j] = cbuf[q][j];
+        const uint32_t fit = res_n[cell[u]];
+        if (pos[u] < fit) {
+            const uint32_t p = cell[u] % SAE_PARTS;
+            cq[(p * SAE_STRIPES + stripe) * SAE_STRIPE_CAP + res_base[cell[u]] + pos[u]] = cbuf[q][i % SCAN_CB];
         } else {
-            const uint32_t p = ovf_base[q] + (j - ovf_n[q]);
-            if (p < SAE_LCAP) cq[SAE_LCAP + p] = cbuf[q][j];
+            const uint32_t at = ovf_base[cell[u]] + (pos[u] - fit);
+            if (at < SAE_LCAP) cq[SAE_LCAP + at] = cbuf[q][i % SCAN_CB];
         }
     }
 }
@@ -1691,7 +1728,6 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
 //    every other workgroup stops and the finisher alone computes everything
 //    by the exact path (radix select streaming the pool) and merges.
 #define FIN_THREADS 1024
-#define FIN_G 16                             // buckets per group workgroup
 #define FIN_GPQ (SAE_NBUCKET / FIN_G)        // group workgroups per queue
 #define FIN_NU 64                            // union workgroups
 #define FIN_GCAP 4096                        // candidates a workgroup ranks at once
@@ -1712,8 +1748,10 @@ struct FinInfo {
     int32_t nb[SAE_MAX_QUEUES];
     int32_t fail[SAE_MAX_QUEUES];
     unsigned long long thr[SAE_MAX_QUEUES];
-    uint32_t spre[SAE_MAX_QUEUES][SAE_STRIPES + 1];  // position of each stripe's first candidate in queue
-                                                     // order; [SAE_STRIPES]: the overflow list's
+    uint32_t ovn[SAE_MAX_QUEUES];                                // candidates in the overflow list
+    uint32_t pn[SAE_MAX_QUEUES * SAE_PARTS];                     // candidates in each range's stripes
+    unsigned long long pe[SAE_MAX_QUEUES * SAE_PARTS];           // the ranges' upper ends
+    uint32_t cn4[SAE_MAX_QUEUES * SAE_PARTS][SAE_STRIPES / 4];   // candidates per stripe, a byte each
     int32_t any_fail, n1, rest, d;
 };
 
@@ -1725,32 +1763,49 @@ struct FinRange {
 // Per-instance facts from the scan's counts (all threads; ends with a barrier).
 __device__ void fin_info(const DevCtx &c, const SelectArgs &a, int inst, uint32_t kq, FinInfo &f)
 {
+    constexpr int NW = FIN_THREADS / SAE_WAVE;
+    constexpr int RPW = SAE_MAX_QUEUES * SAE_PARTS / NW;  // ranges per wave
+    static_assert(RPW * NW == SAE_MAX_QUEUES * SAE_PARTS && SAE_STRIPE_CAP <= 255, "a wave's share; counts fit a byte");
     const int Q = c.Q, tid = threadIdx.x, lane = lane_id(), wave = tid / SAE_WAVE;
-    if (wave < Q) {
-        const long long iq = (long long)inst * Q + wave;
-        const uint32_t *sn = c.stripe_n + iq * (SAE_STRIPES + 1);
-        const uint32_t raw = sn[lane];
-        const uint32_t ovr = sn[SAE_STRIPES];
-        const int32_t nb = c.nsplit[iq];
-        const unsigned long long thr = c.thr[iq];
-        const uint32_t capd = raw < SAE_STRIPE_CAP ? raw : (uint32_t)SAE_STRIPE_CAP;
-        const uint32_t inc = wave_incl_scan(capd);
-        f.spre[wave][lane] = inc - capd;
-        const uint32_t S = __shfl(inc, SAE_WAVE - 1, SAE_WAVE);
+    const long long i0 = (long long)inst * Q;
+    uint32_t raw[RPW];  // range wave + NW r: the stripe counts
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+        const int g = wave + NW * r, q = g / SAE_PARTS;
+        raw[r] = q < Q ? c.stripe_n[(i0 + q) * (SAE_CELLS + 1) + (g % SAE_PARTS) * SAE_STRIPES + lane] : 0u;
+    }
+    if (tid < Q) {
+        const uint32_t ovr = c.stripe_n[(i0 + tid) * (SAE_CELLS + 1) + SAE_CELLS];
+        const int32_t nb = c.nsplit[i0 + tid];
+        const unsigned long long thr = c.thr[i0 + tid];
         const uint32_t ovk = ovr < SAE_LCAP ? ovr : (uint32_t)SAE_LCAP;
-        if (lane == 0) {
-            f.spre[wave][SAE_STRIPES] = S;
-            f.C[wave] = S + ovk;
-            f.over[wave] = ovr - ovk;
-            f.nb[wave] = nb;
-            f.thr[wave] = thr;
-        }
+        f.ovn[tid] = ovk;
+        f.over[tid] = ovr - ovk;
+        f.nb[tid] = nb;
+        f.thr[tid] = thr;
+    } else if (tid < SAE_MAX_QUEUES) {
+        f.ovn[tid] = 0;
+    }
+    if (tid >= SAE_WAVE && tid < SAE_WAVE + SAE_MAX_QUEUES * SAE_PARTS) {
+        const int g = tid - SAE_WAVE;
+        f.pe[g] = g < Q * SAE_PARTS ? c.cend[i0 * SAE_PARTS + g] : ~0ull;
+    }
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+        const int g = wave + NW * r;
+        const uint32_t n = raw[r] < SAE_STRIPE_CAP ? raw[r] : (uint32_t)SAE_STRIPE_CAP;
+        reinterpret_cast<uint8_t *>(f.cn4[g])[lane] = (uint8_t)n;
+        const uint32_t t = wave_sum(n);
+        if (lane == 0) f.pn[g] = t;
     }
     lds_barrier();
     if (tid == 0) {
         int any = 0;
         uint32_t other = 0, n_ef = 0;
         for (int q = 0; q < Q; ++q) {
+            uint32_t C = f.ovn[q];
+            for (int p = 0; p < SAE_PARTS; ++p) C += f.pn[q * SAE_PARTS + p];
+            f.C[q] = C;
             const bool all = f.thr[q] == ~0ull;
             const uint32_t need = (all && f.C[q] < kq) ? f.C[q] : kq;
             const bool fail = need > 0 && ((a.flags & SAE_SS_FORCE_FALLBACK) || f.nb[q] <= 0 || f.C[q] < need ||
@@ -1767,18 +1822,6 @@ __device__ void fin_info(const DevCtx &c, const SelectArgs &a, int inst, uint32_
         f.d = (int32_t)(n_ef + ((uint32_t)f.rest < other ? (uint32_t)f.rest : other));
     }
     lds_barrier();
-}
-
-// Where candidate i (< C) of a queue lies: the stripes in order, then the
-// overflow list.  Computed without a branch, so that the loads of all of a
-// thread's candidates can be in flight together (a load inside a divergent
-// branch is waited for at the branch's end).
-__device__ __forceinline__ uint32_t fin_slot(const uint32_t *spre, uint32_t i)
-{
-    const int s = last_le<6>(spre, SAE_STRIPES, i);
-    const uint32_t in_stripe = (uint32_t)s * SAE_STRIPE_CAP + (i - spre[s]);
-    const uint32_t ov = spre[SAE_STRIPES];
-    return i >= ov ? (uint32_t)SAE_LCAP + (i - ov) : in_stripe;
 }
 
 // One wave's refinement of the segment [sg.x, sg.y) of st2 (more than one and
@@ -1845,8 +1888,12 @@ __device__ __forceinline__ void fin_wave_refine(unsigned long long *st2, uint32_
 // Ranks the candidates of the queues in `src` (a bit mask) that lie in
 // (first range's lo, ends[e1 - 1]]: out(r, e) is called for every one of them
 // whose rank r among all those queues' candidates is below `need`.
-// Streaming: wave w reads stripes w, w + 16, w + 32, w + 48 of a queue, every
-// load issued before any is used, and keeps the candidates inside the range
+// Streaming: of each queue only the candidate ranges that overlap the wanted
+// one are read (the others count as below or are left out), four at a time,
+// wave w their stripes 4 w .. 4 w + 3, every load issued before any is used.
+// A wave's instructions per 64 candidates bound this, not the bytes: reading
+// every queue's candidates whole took a union workgroup 12 to 17 us, its
+// ranges alone take 4.  A wave keeps the candidates inside the wanted range
 // in a region of its own (a register count, no atomics).  Ranking, over those
 // only: each candidate's bucket, the buckets' smallest and largest values, a
 // counting sort by sub-bin (FIN_SB equal value ranges between a bucket's
@@ -1875,7 +1922,8 @@ __device__ void fin_rank(const DevCtx &c, int inst, const FinInfo &f, uint32_t s
     constexpr int WCAP = FIN_GCAP / NW;  // staging slots per wave
     constexpr int PER = FIN_GCAP / FIN_THREADS;
     static_assert(NSB == FIN_THREADS, "one sub-bin per thread in the scan");
-    static_assert(SAE_STRIPES == 4 * NW && SAE_STRIPE_CAP == 4 * SAE_WAVE, "four stripes of four slots per lane");
+    static_assert(SAE_STRIPES == 4 * NW && SAE_STRIPE_CAP == SAE_WAVE, "four stripes per wave, a lane per slot");
+    static_assert(SAE_MAX_QUEUES * SAE_PARTS <= 32, "a range per lane and mask bit");
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / SAE_WAVE;
     __shared__ FinRange stack[FIN_STACK];
     __shared__ int32_t sp_s, stop_s, go_s, full_s;
@@ -1910,49 +1958,73 @@ __device__ void fin_rank(const DevCtx &c, int inst, const FinInfo &f, uint32_t s
         const FinRange r = cur;
         const bool has_ends = r.e1 > r.e0;
         const int nbk = has_ends ? r.e1 - r.e0 : 1;
-        uint32_t below = 0, wn = 0;  // wn: this wave's staged candidates (wave-uniform)
+        uint32_t below = 0, wn = 0;  // this wave's candidates below the range and staged (wave-uniform)
         bool full = false;
         const unsigned long long lt = lanemask_lt();
         unsigned long long *wst = st1 + wave * WCAP;
-        auto take = [&](unsigned long long e, bool ok) {
-            const bool under = ok && r.has_lo && e <= r.lo;
-            below += under ? 1u : 0u;
-            const bool inr = ok && !under && e <= r.hi;
-            const unsigned long long m = __ballot(inr);
-            const uint32_t p = wn + (uint32_t)__popcll(m & lt);
-            if (inr && p < WCAP) wst[p] = e;
-            wn += (uint32_t)__popcll(m);
+        const unsigned long long lo_on = r.has_lo ? ~0ull : 0ull;
+        // up to 64 candidates, those on the lanes of ok: two compares each for
+        // most of them, as few lie inside the range
+        auto take = [&](unsigned long long e, unsigned long long ok) {
+            const unsigned long long under = __ballot(e <= r.lo) & ok & lo_on;
+            const unsigned long long m = __ballot(e <= r.hi) & ok & ~under;
+            below += (uint32_t)__popcll(under);
+            if (m) {  // uniform
+                const uint32_t p = wn + (uint32_t)__popcll(m & lt);
+                if (((m >> lane) & 1ull) && p < WCAP) wst[p] = e;
+                wn += (uint32_t)__popcll(m);
+            }
         };
-        for (int q = 0; q < c.Q; ++q) {
-            if (!((src >> q) & 1u)) continue;
-            const uint32_t C = f.C[q];
-            if (C == 0) continue;  // uniform
-            const unsigned long long *cq = c.cand + ((long long)inst * c.Q + q) * 2 * SAE_LCAP;
-            const uint32_t *spre = f.spre[q];
+        // which candidate ranges lie below this range, and which overlap it (lane
+        // g: range g % SAE_PARTS of queue g / SAE_PARTS)
+        uint32_t todo, ovq;
+        {
+            const int g = lane & 31, q = g / SAE_PARTS;
+            const bool in = lane < 32 && ((src >> q) & 1u) && f.pn[g] > 0;
+            const bool under = in && r.has_lo && f.pe[g] <= r.lo;
+            const bool past = g % SAE_PARTS != 0 && f.pe[g > 0 ? g - 1 : 0] >= r.hi;
+            if (wave == 0) below += wave_sum(under ? f.pn[g] : 0u);  // uniform
+            todo = (uint32_t)__ballot(in && !under && !past);
+            ovq = (uint32_t)__ballot(lane < SAE_MAX_QUEUES && ((src >> lane) & 1u) && f.ovn[lane & (SAE_MAX_QUEUES - 1)] > 0);
+        }
+        while (todo) {  // uniform: up to four ranges at a time, all loads in flight together
             unsigned long long ev[16];
-            uint32_t okm = 0;
+            uint32_t cn4[4];  // candidates in this wave's four stripes of the range, a byte each
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int st = wave + NW * r4;
-                const uint32_t cnt = spre[st + 1] - spre[st];
+            for (int u = 0; u < 4; ++u) {
+                cn4[u] = 0;
+                if (todo) {  // uniform
+                    const int g = __ffs((int)todo) - 1;
+                    todo &= todo - 1u;
+                    const unsigned long long *cg =
+                        c.cand + ((long long)inst * c.Q + g / SAE_PARTS) * 2 * SAE_LCAP +
+                        (g % SAE_PARTS * SAE_STRIPES + wave * 4) * SAE_STRIPE_CAP + lane;
+                    cn4[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)f.cn4[g][wave]);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const uint32_t j = (uint32_t)(lane + SAE_WAVE * v);
-                    ev[r4 * 4 + v] = cq[st * SAE_STRIPE_CAP + (j < cnt ? j : 0u)];
-                    okm |= (j < cnt) ? (1u << (r4 * 4 + v)) : 0u;
+                    for (int t = 0; t < 4; ++t) ev[u * 4 + t] = cg[t * SAE_STRIPE_CAP];  // slots past the count too
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 16; ++u) take(ev[u], (okm >> u) & 1u);
-            // the overflow list (usually empty), split over the waves
-            const uint32_t ov = C - spre[SAE_STRIPES];
+            for (int u = 0; u < 4; ++u)
+                if (cn4[u]) {  // uniform
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const uint32_t n = (cn4[u] >> (8 * t)) & 255u;
+                        take(ev[u * 4 + t], n ? ~0ull >> (64u - n) : 0ull);
+                    }
+                }
+        }
+        // the overflow lists (usually empty), split over the waves
+        for (; ovq; ovq &= ovq - 1u) {  // uniform
+            const int q = __ffs((int)ovq) - 1;
+            const uint32_t ov = f.ovn[q];
+            const unsigned long long *cq = c.cand + ((long long)inst * c.Q + q) * 2 * SAE_LCAP + SAE_LCAP;
             for (uint32_t b0 = 0; b0 < ov; b0 += FIN_THREADS) {
                 const uint32_t i = b0 + (uint32_t)tid;
-                take(cq[SAE_LCAP + (i < ov ? i : ov - 1)], i < ov);
+                take(cq[i < ov ? i : ov - 1], __ballot(i < ov));
             }
         }
         full = wn > WCAP;
-        for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, SAE_WAVE);
         if (lane == 0) {
             if (below) atomicAdd(&below_s, below);
             wcnt[wave] = wn < WCAP ? wn : WCAP;

@@ -26,12 +26,17 @@
 // upper ends are sampled (key, id) values at or below the candidate bound.
 #define SAE_NBUCKET 256  // buckets
 #define SAE_LCAP 16384   // candidates kept per (instance, queue)
-// The scan appends a queue's candidates to one of SAE_STRIPES stripes of
-// SAE_LCAP / SAE_STRIPES slots (one device atomic per workgroup and queue,
-// spread over the stripes so that few workgroups meet on one counter); what
-// does not fit a stripe goes to the queue's overflow list of SAE_LCAP slots.
+// The scan divides a queue's candidates into SAE_PARTS ranges of value with
+// about as many candidates each (a workgroup of the ranking then reads the one
+// or two ranges it ranks, not all candidates) and appends a range's to one of
+// SAE_STRIPES stripes of SAE_STRIPE_CAP slots (one device atomic per workgroup
+// and range, spread over the stripes so that few workgroups meet on one
+// counter); what does not fit a stripe goes to the queue's overflow list of
+// SAE_LCAP slots.
+#define SAE_PARTS 4
 #define SAE_STRIPES 64
-#define SAE_STRIPE_CAP (SAE_LCAP / SAE_STRIPES)
+#define SAE_STRIPE_CAP (SAE_LCAP / (SAE_PARTS * SAE_STRIPES))
+#define SAE_CELLS (SAE_PARTS * SAE_STRIPES)
 
 // Feedback counters are added into one of SAE_CSLOTS striped copies (chosen by
 // the adding workgroup) and folded into InstState by the learner kernel:
@@ -138,9 +143,10 @@ struct DevCtx {
     uint32_t *sel_stats;       // [n_inst][Q][4] last pool scan: evictable, candidates, beyond a stripe, slow path
     unsigned long long *split; // [n_inst][Q][SAE_NBUCKET] bucket upper ends, ascending; the last is thr
     int32_t *nsplit;           // [n_inst][Q] buckets (0: no candidates)
+    unsigned long long *cend;  // [n_inst][Q][SAE_PARTS] upper ends of the candidate ranges, the last one ~0
     unsigned long long *cand;  // [n_inst][Q][2 SAE_LCAP] candidates, unordered: the stripes
-                               // (SAE_STRIPES x SAE_STRIPE_CAP), then the overflow list
-    uint32_t *stripe_n;        // [n_inst][Q][SAE_STRIPES + 1] slots taken in each stripe (may exceed its
+                               // (SAE_PARTS x SAE_STRIPES x SAE_STRIPE_CAP), then the overflow list
+    uint32_t *stripe_n;        // [n_inst][Q][SAE_CELLS + 1] slots taken in each stripe (may exceed its
                                // capacity: the rest went to the overflow list), then in the overflow list
     int32_t scan_gx;           // scan workgroups per instance
     int32_t n_cu;              // compute units of the device
