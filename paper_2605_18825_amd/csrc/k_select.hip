@@ -1355,6 +1355,77 @@ __global__ void __launch_bounds__(SEL_THREADS) k_match_prep(DevCtx c, SelectArgs
     }
 }
 
+// The bucket ends of all queues but the evict-first one merged, up to the
+// smallest of those queues' bounds: between consecutive ones lies at most one
+// bucket's worth of each queue, wherever each queue's keys lie, so they cut
+// the decision's second stage into equal shares of work.  (A queue that turns
+// out to hold nothing has the bound ~0, so it does not move the smallest one,
+// and its ends are only further cuts.)  By one workgroup of the scan's launch,
+// beside the scan: every workgroup of the ranking needs the merged ends, and
+// merging them there took each 3 to 4 us before it read its first candidate
+// (k_final of a step of 262,144 blocks 16.0 us, now 13.4; the scan is 0.3 us longer).
+// eq: Q SAE_NBUCKET values of LDS.
+__device__ __forceinline__ void merge_ends(const DevCtx &c, int inst, unsigned long long *eq)
+{
+    constexpr int PER = SAE_MAX_QUEUES * SAE_NBUCKET / SCAN_THREADS;  // one queue's ends at a time
+    static_assert(SCAN_THREADS == SAE_NBUCKET && PER == SAE_MAX_QUEUES, "a thread per bucket of a queue");
+    __shared__ int32_t n_s[SAE_MAX_QUEUES];
+    const int Q = c.Q, tid = threadIdx.x;
+    unsigned long long v[PER], rb = ~0ull;
+    int nq[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const bool in = q < Q && q != c.ef_queue;
+        const long long iq = (long long)inst * Q + (in ? q : 0);
+        nq[q] = in ? c.nsplit[iq] : 0;
+        const unsigned long long t = c.thr[iq];
+        v[q] = c.split[iq * SAE_NBUCKET + tid];
+        rb = nq[q] > 0 && t < rb ? t : rb;
+    }
+    if (tid < SAE_MAX_QUEUES) n_s[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const bool ok = tid < nq[q] && v[q] <= rb;
+        v[q] = ok ? v[q] : ~0ull;  // past a queue's ends: last
+        if (q < Q) eq[q * SAE_NBUCKET + tid] = v[q];
+        const int n = __popcll(__ballot(ok));
+        if (lane_id() == 0 && n) atomicAdd(&n_s[q], n);
+    }
+    __syncthreads();
+    // each end's rank in the merge, equal ends ordered by queue: its place
+    // among every other queue's ends, searched side by side
+    int n[PER], m = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        n[q] = __builtin_amdgcn_readfirstlane(n_s[q]);
+        m += n[q];
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if (n[q] == 0) continue;  // uniform
+        int l[PER];
+#pragma unroll
+        for (int q2 = 0; q2 < PER; ++q2) l[q2] = 0;
+        auto step = [&](int st) {  // adds st where the end st - 1 places on is below
+#pragma unroll
+            for (int q2 = 0; q2 < PER; ++q2) {
+                if (q2 == q || n[q2] == 0) continue;  // uniform
+                const unsigned long long e = eq[q2 * SAE_NBUCKET + l[q2] + st - 1];
+                l[q2] += (q2 < q ? e <= v[q] : e < v[q]) ? st : 0;
+            }
+        };
+#pragma unroll 1
+        for (int st = SAE_NBUCKET / 2; st > 0; st >>= 1) step(st);
+        step(1);
+        int r = tid;
+#pragma unroll
+        for (int q2 = 0; q2 < PER; ++q2) r += l[q2];
+        if (tid < n[q]) c.mend[(long long)inst * Q * SAE_NBUCKET + r] = v[q];
+    }
+    if (tid == 0) c.n_mend[inst] = m;
+}
+
 // Pool-scan engine, step 3: one streaming pass over the whole pool.
 // Each wave takes batches of SCAN_BATCH consecutive blocks (4 per lane, read
 // with 16-, 8- and 16-byte loads of last_access, meta and off), with the
@@ -1490,7 +1561,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
     __shared__ uint32_t res_n[SAE_MAX_QUEUES * SAE_PARTS], res_base[SAE_MAX_QUEUES * SAE_PARTS],
         ovf_base[SAE_MAX_QUEUES * SAE_PARTS];
     const int inst = blockIdx.y;
-    const int wg = blockIdx.x;
+    const int wg = (int)blockIdx.x - 1;  // the first workgroup merges the bucket ends
     const int Q = c.Q;
     const int N = c.N;
     const long long base = (long long)inst * N;
@@ -1500,7 +1571,12 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
     const QuadRange qr = quad_range(c, inst);
     const int nfull = (qr.nvec + SAE_WAVE - 1) / SAE_WAVE;  // batches read with vector loads
     const int gw = wg * SCAN_WAVES + wave;
-    const int tw = (int)gridDim.x * SCAN_WAVES;
+    const int tw = ((int)gridDim.x - 1) * SCAN_WAVES;
+    if (wg < 0) {
+        static_assert(sizeof(s_lst) >= SAE_MAX_QUEUES * SAE_NBUCKET * sizeof(unsigned long long), "LDS for the ends");
+        merge_ends(c, inst, reinterpret_cast<unsigned long long *>(s_lst));
+        return;
+    }
     // the first two batches' loads go out before the tables are read
     auto ld = [&](int bi) {
         const int i = bi * SAE_WAVE + lane;
@@ -2391,15 +2467,18 @@ __global__ void __launch_bounds__(FIN_THREADS) k_final(DevCtx c, SelectArgs a, i
         const unsigned long long *spl = c.split + ((long long)inst * Q + unit / FIN_GPQ) * SAE_NBUCKET;
         ends[tid] = (b0 + tid - 1 >= 0) ? spl[b0 + tid - 1] : 0ull;
     }
-    // a union workgroup's: every queue's bucket ends (2 per thread, Q <= 8)
-    static_assert(SAE_MAX_QUEUES * SAE_NBUCKET == 2 * FIN_THREADS, "two bucket ends per thread");
+    // a union workgroup's: all merged ends (2 per thread, Q <= 8), as which of
+    // them it needs depends on their number
+    static_assert(SAE_MAX_QUEUES * SAE_NBUCKET == 2 * FIN_THREADS, "two ends per thread");
     unsigned long long uend[2] = {0ull, 0ull};
+    int n_mend = 0;
     if (unit >= n_group && unit < n_group + FIN_NU) {
-        const unsigned long long *spl = c.split + (long long)inst * Q * SAE_NBUCKET;
+        const unsigned long long *me = c.mend + (long long)inst * Q * SAE_NBUCKET;
+        n_mend = c.n_mend[inst];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int i = tid + h * FIN_THREADS;
-            uend[h] = (i < Q * SAE_NBUCKET) ? spl[i] : 0ull;
+            uend[h] = (i < Q * SAE_NBUCKET) ? me[i] : 0ull;
         }
     }
     fin_info(c, a, inst, kq, f);
@@ -2439,58 +2518,13 @@ __global__ void __launch_bounds__(FIN_THREADS) k_final(DevCtx c, SelectArgs a, i
             first.e0 = 1;
             first.e1 = 1 + (b1 - b0);
         } else {
-            // The union's ranges follow the bucket ends of all its queues
-            // merged, up to the reference bound: a range between consecutive
-            // merged ends holds at most one bucket's worth of each queue,
-            // wherever each queue's keys lie.  Union workgroup g takes
-            // consecutive merged ends g S .. g S + S - 1, S = ceil(M / FIN_NU).
-            unsigned long long *mend = st1, *mer = st2;  // [queue][SAE_NBUCKET], merged
-            __shared__ uint32_t mcnt[SAE_MAX_QUEUES], mtot;
-            const unsigned long long rb = f.thr[rq];
+            // Union workgroup g takes the merged ends g S .. g S + S - 1,
+            // S = ceil(M / FIN_NU) (merge_ends).
+            unsigned long long *mer = st1;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int i = tid + h * FIN_THREADS, qq = i / SAE_NBUCKET, j = i % SAE_NBUCKET;
-                const bool ok = qq < Q && ((src >> qq) & 1u) && j < f.nb[qq];
-                mend[i] = ok ? uend[h] : ~0ull;  // ascending per queue, unused slots last
-            }
+            for (int h = 0; h < 2; ++h) mer[tid + h * FIN_THREADS] = uend[h];
             lds_barrier();
-            if (tid < SAE_MAX_QUEUES) {  // each queue's ends at or below the reference bound
-                const int nq = (tid < Q && ((src >> tid) & 1u)) ? f.nb[tid] : 0;
-                const unsigned long long *eq = mend + tid * SAE_NBUCKET;
-                int l = 0;
-#pragma unroll
-                for (int st = SAE_NBUCKET; st > 0; st >>= 1)
-                    if (l + st <= nq && eq[l + st - 1] <= rb) l += st;
-                mcnt[tid] = (uint32_t)l;
-            }
-            lds_barrier();
-            if (tid == 0) {
-                uint32_t m = 0;
-                for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq) m += mcnt[qq];
-                mtot = m;
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int i = tid + h * FIN_THREADS, qq = i / SAE_NBUCKET, j = i % SAE_NBUCKET;
-                if ((uint32_t)j < mcnt[qq]) {
-                    // rank in the merge, equal ends ordered by queue
-                    const unsigned long long v = mend[i];
-                    uint32_t r = (uint32_t)j;
-                    for (int q2 = 0; q2 < SAE_MAX_QUEUES; ++q2) {
-                        if (q2 == qq || mcnt[q2] == 0) continue;
-                        const unsigned long long *e2 = mend + q2 * SAE_NBUCKET;
-                        const int n2 = (int)mcnt[q2];
-                        int l = 0;
-#pragma unroll
-                        for (int st = SAE_NBUCKET; st > 0; st >>= 1)
-                            if (l + st <= n2 && (q2 < qq ? e2[l + st - 1] <= v : e2[l + st - 1] < v)) l += st;
-                        r += (uint32_t)l;
-                    }
-                    mer[r] = v;
-                }
-            }
-            lds_barrier();
-            const uint32_t M = mtot;
+            const uint32_t M = (uint32_t)n_mend;
             const uint32_t S = (M + FIN_NU - 1) / FIN_NU;
             const uint32_t g = (uint32_t)(unit - n_group);
             const uint32_t r0 = g * S;
@@ -3705,9 +3739,9 @@ hipError_t launch_select_scan(const DevCtx &c, const SelectArgs &a, hipStream_t 
     }
     // step 3: streaming pass (with profiling, the events carry the dispatch's own start and end)
     if (ev0 && ev1)
-        hipExtLaunchKernelGGL(k_scan, dim3(c.scan_gx, c.n_inst), dim3(SCAN_THREADS), 0, s, ev0, ev1, 0, c, a);
+        hipExtLaunchKernelGGL(k_scan, dim3(c.scan_gx + 1, c.n_inst), dim3(SCAN_THREADS), 0, s, ev0, ev1, 0, c, a);
     else
-        hipLaunchKernelGGL(k_scan, dim3(c.scan_gx, c.n_inst), dim3(SCAN_THREADS), 0, s, c, a);
+        hipLaunchKernelGGL(k_scan, dim3(c.scan_gx + 1, c.n_inst), dim3(SCAN_THREADS), 0, s, c, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // step 4: lists, decision and commit
     const int P = pow2_at_least(c.max_k);

@@ -143,6 +143,9 @@ struct DevCtx {
     uint32_t *sel_stats;       // [n_inst][Q][4] last pool scan: evictable, candidates, beyond a stripe, slow path
     unsigned long long *split; // [n_inst][Q][SAE_NBUCKET] bucket upper ends, ascending; the last is thr
     int32_t *nsplit;           // [n_inst][Q] buckets (0: no candidates)
+    unsigned long long *mend;  // [n_inst][Q SAE_NBUCKET] the decision's bucket ends: all queues' but the
+                               // evict-first one's, merged, up to the smallest of their bounds
+    int32_t *n_mend;           // [n_inst] their number
     unsigned long long *cend;  // [n_inst][Q][SAE_PARTS] upper ends of the candidate ranges, the last one ~0
     unsigned long long *cand;  // [n_inst][Q][2 SAE_LCAP] candidates, unordered: the stripes
                                // (SAE_PARTS x SAE_STRIPES x SAE_STRIPE_CAP), then the overflow list

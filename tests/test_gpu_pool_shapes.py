@@ -142,6 +142,31 @@ def test_scan_clusters_of_equal_keys(size):
     several(2, 40009, 3000, api.SS_ENGINE_SCAN, edit=same_time)
 
 
+@pytest.mark.parametrize("kinds", ["E", "L", "ER", "RS", "ELL", "LSRLSRLS", "ERSLRSLL"])
+@pytest.mark.parametrize("k", [1, 700, 4000])
+def test_scan_queue_counts(kinds, k):
+    """One to eight queues, with and without an evict-first one, of very unequal sizes (one empty, one of a few
+    blocks): the merged bucket ends and the candidate ranges of every combination."""
+    names = dict(E=api.KIND_EVICT_FIRST, L=api.KIND_LOGNORMAL, R=api.KIND_RECENCY, S=api.KIND_STRUCTURAL)
+    Q = len(kinds)
+    pool = synth.make_pool(synth.pool_config("large"), n_blocks=50021, seed=100 * Q + k)
+    rng = np.random.default_rng(k)
+    share = np.array([0.6 ** q for q in range(Q)])
+    if Q >= 3:
+        share[Q - 1] = 0.0
+    pool["queue"] = rng.choice(Q, 50021, p=share / share.sum()).astype(pool["queue"].dtype)
+    if Q >= 3:
+        pool["queue"][rng.choice(50021, 40, replace=False)] = Q - 2
+    p = Pair([names[x] for x in kinds], pool, k, mu=[5.0 + 0.5 * q for q in range(Q)], sigma=[1.0] * Q, K=k)
+    try:
+        for t in (0, 300):
+            say("scan: queues %s, k %d" % (kinds, k))
+            p.select(pool["now"] + t, k, flags=api.SS_ENGINE_SCAN)
+        assert not p.status()
+    finally:
+        p.close()
+
+
 # one wave, one workgroup round, the LDS key cache's limit and the sorts' segment sizes
 @pytest.mark.parametrize("N,k", [(1, 1), (63, 2), (1024, 128), (1025, 129), (8192, 256), (8193, 100), (9001, 1)])
 def test_batched_small_pools(N, k):
