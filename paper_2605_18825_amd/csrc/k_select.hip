@@ -1455,6 +1455,8 @@ __device__ __forceinline__ void merge_ends(const DevCtx &c, int inst, unsigned l
 #define SCAN_WAVES (SCAN_THREADS / SAE_WAVE)
 #define SCAN_LIST (SAE_WAVE + SCAN_BATCH)  // queued blocks per wave
 #define SCAN_CB 128  // candidates a workgroup buffers per queue before appending to a stripe
+#define SCAN_PIECE 16  // candidates of one range a workgroup appends to one stripe
+#define SCAN_PIECES (SCAN_CB / SCAN_PIECE)
 
 // Structural (pn / pd = 1 - o_b / o_max) and recency (pn = pd = 1) blocks:
 // true only if fl(pn awl) > fl(fl(T dt) pd), which implies P > T.  Proof
@@ -1558,11 +1560,9 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
     __shared__ uint32_t left_s[SCAN_WAVES + 1];
     __shared__ int4 s_lst[SCAN_WAVES][SCAN_LIST];  // queued blocks: last_access, off, meta, id
     __shared__ unsigned long long cbuf[SAE_MAX_QUEUES][SCAN_CB];  // this workgroup's candidates per queue
-    // per queue and range: upper end, candidates, first slot in the stripe and,
-    // past its capacity, in the overflow list
+    // per queue and range: upper end, candidates
     __shared__ unsigned long long cend_s[SAE_MAX_QUEUES * SAE_PARTS];
-    __shared__ uint32_t res_n[SAE_MAX_QUEUES * SAE_PARTS], res_base[SAE_MAX_QUEUES * SAE_PARTS],
-        ovf_base[SAE_MAX_QUEUES * SAE_PARTS];
+    __shared__ uint32_t res_n[SAE_MAX_QUEUES * SAE_PARTS];
     const int inst = blockIdx.y;
     const int wg = (int)blockIdx.x - 1;  // the first workgroup merges the bucket ends
     const int Q = c.Q;
@@ -1731,9 +1731,16 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
     }
     if (st) atomicOr(&st_s, st);
     lds_barrier();
-    // the buffered candidates go to stripe wg mod SAE_STRIPES of their queue
-    // and range (one reservation each), what does not fit it to the queue's
-    // overflow list (a second reservation, rarely); then every thread stores
+    // the buffered candidates of a queue and range go, in pieces of SCAN_PIECE
+    // (mostly there is one), to stripes that lie a quarter of the stripes and
+    // then an eighth apart (one reservation each), what does not fit a stripe to
+    // the queue's overflow list (a second reservation, rarely); then every
+    // thread stores.  More than one piece comes from blocks of equal keys whose
+    // ids follow each other (an evict-first queue of full blocks): all of a
+    // range's candidates are then in some tens of workgroups, and in one stripe
+    // per workgroup they filled those and the overflow list, and with them a
+    // ranking wave's region (k_final 13 to 385 us, 52 on average, now 16,
+    // on such a pool of 4,194,304 blocks)
     constexpr int PUT = SAE_MAX_QUEUES * SCAN_CB / SCAN_THREADS;
     static_assert(PUT * SCAN_THREADS == SAE_MAX_QUEUES * SCAN_CB, "a thread's share of the buffers");
     uint32_t cell[PUT], pos[PUT];  // queue and range, position among this workgroup's; cell ~0: none
@@ -1752,16 +1759,29 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
         }
     }
     lds_barrier();
-    const uint32_t stripe = (uint32_t)wg % SAE_STRIPES;
-    if (tid < Q * SAE_PARTS) {
-        const int q = tid / SAE_PARTS, p = tid % SAE_PARTS;
-        const uint32_t n = res_n[tid];
+    // per piece: first slot in its stripe, those that fit, and the others' first
+    // slot in the overflow list; where the queued blocks were (free since the
+    // last scoring: with LDS of its own a compute unit held four workgroups
+    // instead of five, and the one that merges the ends ran after the others,
+    // 3 to 5 us)
+    uint32_t *pc_base = reinterpret_cast<uint32_t *>(s_lst);
+    uint32_t *pc_fit = pc_base + SAE_MAX_QUEUES * SAE_PARTS * SCAN_PIECES;
+    uint32_t *pc_ovf = pc_fit + SAE_MAX_QUEUES * SAE_PARTS * SCAN_PIECES;
+    static_assert(sizeof(s_lst) >= 3 * SAE_MAX_QUEUES * SAE_PARTS * SCAN_PIECES * sizeof(uint32_t), "LDS for the pieces");
+    auto stripe_of = [&](uint32_t j) {  // piece j of this workgroup
+        return ((uint32_t)wg + j * (SAE_STRIPES / 4) + (j >> 2) * (SAE_STRIPES / 8)) % SAE_STRIPES;
+    };
+    static_assert(SAE_MAX_QUEUES * SAE_PARTS * SCAN_PIECES <= SCAN_THREADS, "a thread per piece");
+    if (tid < Q * SAE_PARTS * SCAN_PIECES) {
+        const int g = tid / SCAN_PIECES, q = g / SAE_PARTS, p = g % SAE_PARTS;
+        const uint32_t j = (uint32_t)(tid % SCAN_PIECES), all = res_n[g];
+        const uint32_t n = all > j * SCAN_PIECE ? min(all - j * SCAN_PIECE, (uint32_t)SCAN_PIECE) : 0u;
         uint32_t *sn = stripe_n + q * (SAE_CELLS + 1);
-        const uint32_t b = n ? atomicAdd(&sn[p * SAE_STRIPES + stripe], n) : 0u;
+        const uint32_t b = n ? atomicAdd(&sn[p * SAE_STRIPES + stripe_of(j)], n) : 0u;
         const uint32_t fit = b >= SAE_STRIPE_CAP ? 0u : min(n, (uint32_t)SAE_STRIPE_CAP - b);
-        res_base[tid] = b;
-        res_n[tid] = fit;  // from here those that fit the stripe
-        ovf_base[tid] = (n > fit) ? atomicAdd(&sn[SAE_CELLS], n - fit) : 0u;
+        pc_base[tid] = b;
+        pc_fit[tid] = fit;
+        pc_ovf[tid] = (n > fit) ? atomicAdd(&sn[SAE_CELLS], n - fit) : 0u;
     }
     if (tid == 0) set_status(c.status, st_s);
     lds_barrier();
@@ -1770,13 +1790,14 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
         if (cell[u] == ~0u) continue;
         const int i = tid + u * SCAN_THREADS, q = i / SCAN_CB;
         unsigned long long *cq = cand + (long long)q * 2 * SAE_LCAP;
-        const uint32_t fit = res_n[cell[u]];
-        if (pos[u] < fit) {
+        const uint32_t j = pos[u] / SCAN_PIECE, at = pos[u] % SCAN_PIECE, pc = cell[u] * SCAN_PIECES + j;
+        const uint32_t fit = pc_fit[pc];
+        if (at < fit) {
             const uint32_t p = cell[u] % SAE_PARTS;
-            cq[(p * SAE_STRIPES + stripe) * SAE_STRIPE_CAP + res_base[cell[u]] + pos[u]] = cbuf[q][i % SCAN_CB];
+            cq[(p * SAE_STRIPES + stripe_of(j)) * SAE_STRIPE_CAP + pc_base[pc] + at] = cbuf[q][i % SCAN_CB];
         } else {
-            const uint32_t at = ovf_base[cell[u]] + (pos[u] - fit);
-            if (at < SAE_LCAP) cq[SAE_LCAP + at] = cbuf[q][i % SCAN_CB];
+            const uint32_t o = pc_ovf[pc] + (at - fit);
+            if (o < SAE_LCAP) cq[SAE_LCAP + o] = cbuf[q][i % SCAN_CB];
         }
     }
 }
@@ -1810,7 +1831,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
 #define FIN_GPQ (SAE_NBUCKET / FIN_G)        // group workgroups per queue
 #define FIN_NU 64                            // union workgroups
 #define FIN_GCAP 4096                        // candidates a workgroup ranks at once
-#define FIN_STACK 80                         // pending ranges (a range splits into two)
+#define FIN_STACK 120                        // pending ranges (a range splits into two)
 #define FIN_SB 64                            // sub-bins per bucket in the ranking
 #define FIN_T 64                             // largest segment ranked by comparison alone
 #define FIN_RSTACK (FIN_GCAP / FIN_T)        // pending segments (disjoint, each above FIN_T)
@@ -2027,6 +2048,8 @@ __device__ void fin_rank(const DevCtx &c, int inst, const FinInfo &f, uint32_t s
             cur = stack[--sp_s];
             below_s = 0;
             full_s = 0;
+            rmin_s = ~0ull;
+            rmax_s = 0;
         }
         hist[tid] = 0;
         if (tid < 16) {
@@ -2104,6 +2127,18 @@ __device__ void fin_rank(const DevCtx &c, int inst, const FinInfo &f, uint32_t s
             }
         }
         full = wn > WCAP;
+        if (full) {  // uniform, rare: the values a split goes by
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            unsigned long long mn = ~0ull, mx = 0;
+            for (int i = lane; i < WCAP; i += SAE_WAVE) {
+                const unsigned long long e = wst[i];
+                mn = e < mn ? e : mn;
+                mx = e > mx ? e : mx;
+            }
+            atomicMin(&rmin_s, mn);
+            atomicMax(&rmax_s, mx);
+        }
         if (lane == 0) {
             if (below) atomicAdd(&below_s, below);
             wcnt[wave] = wn < WCAP ? wn : WCAP;
@@ -2133,8 +2168,14 @@ __device__ void fin_rank(const DevCtx &c, int inst, const FinInfo &f, uint32_t s
                     a2.lo = ends[mid - 1];
                     a2.has_lo = 1;
                 } else {
+                    // half way between the staged candidates' smallest and
+                    // largest value (both halves then hold some; half of the
+                    // value range instead split the first bucket, which begins
+                    // at 0, some 40 times before it cut one cluster of keys),
+                    // nested so deep that only a halved value range is sure to end
                     const unsigned long long lo = r.has_lo ? r.lo : 0ull;
-                    const unsigned long long m = lo + (r.hi - lo) / 2;
+                    const unsigned long long m = sp_s < FIN_STACK / 3 ? rmin_s + (rmax_s - rmin_s) / 2
+                                                                      : lo + (r.hi - lo) / 2;
                     a1.e0 = a1.e1 = a2.e0 = a2.e1 = 0;
                     a1.hi = m;
                     a2.lo = m;

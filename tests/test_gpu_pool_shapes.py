@@ -67,6 +67,20 @@ def test_scan_large_odd_pool():
     assert several(1, 700001, 1000, api.SS_ENGINE_SCAN) == []
 
 
+@pytest.mark.parametrize("N,k,mix", [(300001, 1000, None), (262144, 4096, [0.6, 0.1, 0.1, 0.1, 0.1]),
+                                     (1048576, 300, [0.96, 0.01, 0.01, 0.01, 0.01])])
+def test_equal_keys_in_id_order(N, k, mix):
+    """Every queue's keys are equal per type, so its candidates are the lowest
+    ids, all in a few workgroups of the scan: they take several pieces of their
+    stripes, the overflow list where a buffer is full, and splits by value in
+    the ranking."""
+    def edit(pool, rng):
+        pool["last_access"][:] = synth.pools.NOW - 5000
+
+    say("equal keys: %d blocks, k %d" % (N, k))
+    assert several(1, N, k, api.SS_ENGINE_SCAN, edit=edit, mix=mix) == []
+
+
 def test_largest_k_without_fallback():
     """k = 8,192 on 4M blocks: about 16,000 candidates per queue, more than the
     stripes alone hold; their overflow list takes the rest and the exact slow
