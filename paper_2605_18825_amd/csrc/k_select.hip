@@ -3824,9 +3824,14 @@ hipError_t launch_select_batched(const DevCtx &c, const SelectArgs &a, hipStream
     // a large pool adds the streaming list, a small one the key cache, where they fit
     int list_at = -1, cache_at = -1;
     const size_t most = 156 * 1024;  // of the 160 KiB, the rest for the static part
-    if (c.N >= BATCH_STREAM_N && lds + (size_t)BATCH_LIST * 8 <= most) {
-        list_at = (int)(lds / 8);
-        lds += (size_t)BATCH_LIST * 8;
+    // (the list and lists of max_k are never there together: with a large max_k
+    // the list takes part of their room, and the kernel streams where the
+    // call's k fits before it; 256 x 65,536 blocks, k = 256, max_k = 4,096:
+    // 130 us and 174 MB of traffic, cached 160 us and 453 MB)
+    const size_t before = lds < most - (size_t)BATCH_LIST * 8 ? lds : most - (size_t)BATCH_LIST * 8;
+    if (c.N >= BATCH_STREAM_N && before >= h && before >= (size_t)BATCH_LQ_BYTES) {
+        list_at = (int)(before / 8);
+        if (lds < before + (size_t)BATCH_LIST * 8) lds = before + (size_t)BATCH_LIST * 8;
     } else if (c.N <= BATCH_LDS_N && lds + (size_t)c.N * 5 <= most) {
         cache_at = (int)(lds / 8);
         lds += ((size_t)c.N * 5 + 15) / 16 * 16;

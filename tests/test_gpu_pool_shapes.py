@@ -67,6 +67,14 @@ def test_scan_large_odd_pool():
     assert several(1, 700001, 1000, api.SS_ENGINE_SCAN) == []
 
 
+@pytest.mark.parametrize("N", [16384, 40003])
+def test_batched_small_k_under_a_large_max_k(N):
+    """max_k leaves no room for its lists and the streaming list together:
+    instances with a small k stream, the ones with a large k use the cache."""
+    say("batched: %d blocks, max_k 2,048" % N)
+    several(3, N, 2048, api.SS_ENGINE_BATCHED, k_per=[300, 2048, 1])
+
+
 @pytest.mark.parametrize("N,k,mix", [(300001, 1000, None), (262144, 4096, [0.6, 0.1, 0.1, 0.1, 0.1]),
                                      (1048576, 300, [0.96, 0.01, 0.01, 0.01, 0.01])])
 def test_equal_keys_in_id_order(N, k, mix):
