@@ -1419,9 +1419,11 @@ __device__ __forceinline__ void merge_ends(const DevCtx &c, int inst, unsigned l
 #pragma unroll 1
         for (int st = SAE_NBUCKET / 2; st > 0; st >>= 1) step(st);
         step(1);
+        // an end at ~0 (the last one of a queue whose bound admits everything)
+        // equals the padding, which is no end: at most n[q2] of queue q2 precede
         int r = tid;
 #pragma unroll
-        for (int q2 = 0; q2 < PER; ++q2) r += l[q2];
+        for (int q2 = 0; q2 < PER; ++q2) r += l[q2] < n[q2] ? l[q2] : n[q2];
         if (tid < n[q]) c.mend[(long long)inst * Q * SAE_NBUCKET + r] = v[q];
     }
     if (tid == 0) c.n_mend[inst] = m;

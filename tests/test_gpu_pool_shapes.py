@@ -189,6 +189,44 @@ def test_scan_queue_counts(kinds, k):
         p.close()
 
 
+# Every queue's bound admits all of its blocks (its last bucket end is the largest value there is, as in the
+# other queues) and k takes every evictable block or nearly so: the decision reaches the last merged ends, several
+# of which make one share of the ranking.  Evictable blocks per queue, evict-first one first.
+@pytest.mark.parametrize("N,sizes", [(20000, [0, 1300, 900, 390]), (20000, [25, 700, 600, 500]),
+                                     (20000, [0, 1500, 140]), (20000, [3, 300, 1, 0, 2000, 131]),
+                                     (20000, [0, 40, 30, 0, 20]), (4096, [0, 1100, 800, 600]), (300, [10, 60, 50, 40])])
+def test_scan_takes_every_block(N, sizes):
+    kinds = [api.KIND_EVICT_FIRST] + [[api.KIND_LOGNORMAL, api.KIND_RECENCY, api.KIND_STRUCTURAL][q % 3]
+                                      for q in range(len(sizes) - 1)]
+    Q, total = len(sizes), sum(sizes)
+    pool = synth.make_pool(synth.pool_config("large"), n_blocks=N, seed=N + total)
+    rng = np.random.default_rng(total)
+    leaves = np.setdiff1d(np.arange(N), pool["parent"])
+    free = rng.permutation(leaves)[:total]
+    pool["ref_count"][:] = 1
+    pool["ref_count"][free] = 0
+    pool["queue"][:] = 1
+    pool["queue"][free] = np.repeat(np.arange(Q), sizes)
+    fl = api.SS_ENGINE_SCAN if N <= 16384 else 0  # a single larger cache is scanned without being asked
+    p = Pair(kinds, pool, 4096, mu=[6.0 + q for q in range(Q)], sigma=[1.2] * Q, K=4096)
+    R, L = synth.make_requests(pool["chains"], 8, 16, 0.9, 3)
+    try:
+        # the scores and with them the merged ends change from call to call
+        for t, k in ((0, total), (70000, total + 9), (400000, total - 2), (3000000, total)):
+            say("scan: %d blocks, evictable %s, k %d" % (N, sizes, k))
+            p.out.decision.fill_(-1)
+            p.select(pool["now"] + t, k, flags=fl)
+        p.out.decision.fill_(-1)
+        p.match_select(R, L, pool["now"] + 4000000, api.PM_TOUCH, pool["now"] + 4000000, total, fl)
+        p.out.decision.fill_(-1)
+        p.select(pool["now"] + 5000000, total - 4, flags=fl, commit=True)
+        p.check_pool()
+        p.check_counters()
+        assert not p.status()
+    finally:
+        p.close()
+
+
 # one wave, one workgroup round, the LDS key cache's limit and the sorts' segment sizes
 @pytest.mark.parametrize("N,k", [(1, 1), (63, 2), (1024, 128), (1025, 129), (8192, 256), (8193, 100), (9001, 1)])
 def test_batched_small_pools(N, k):
