@@ -310,6 +310,11 @@ __device__ __forceinline__ int probe_hash(const ProbeGroup &a, unsigned long lon
 }
 
 // Claims a slot for h from the p-th slot of its probe sequence on; its index, or -1.
+// What became of a slot another thread was quicker to take is read from the
+// compare-and-swap, not loaded again: a plain load may keep returning the old
+// hash from this die's L2.  A slot that holds a hash by then, or is lost a second
+// time, is passed by (it was not empty then, so no search ends at it), so every
+// round moves on and the search ends after the probe limit.
 template <typename Slot>
 __device__ __forceinline__ long long probe_claim(Slot *tab, uint32_t mask, unsigned long long h, int p)
 {
@@ -321,8 +326,10 @@ __device__ __forceinline__ long long probe_claim(Slot *tab, uint32_t mask, unsig
         p += at;
         if (at == PROBE_G || p >= lim) continue;
         const uint32_t s = (home + (uint32_t)p) & mask;
-        if (atomicCAS(&tab[s].hash, v, h) == v) return (long long)s;
-        // lost the slot: look at it again (another hash has it now)
+        const unsigned long long w = atomicCAS(&tab[s].hash, v, h);
+        if (w == v) return (long long)s;
+        if ((w == SAE_EMPTY_HASH || w == SAE_TOMB_HASH) && atomicCAS(&tab[s].hash, w, h) == w) return (long long)s;
+        ++p;
     }
     return -1;
 }

@@ -29,7 +29,10 @@ def hashes_at_home(back, n, spread):
     return np.array(out, np.uint64)
 
 
-@pytest.mark.parametrize("N,k,back,spread", [(32, 8, 3, 0), (64, 16, 0, 0), (100, 33, 7, 3), (300, 64, 9, 12)])
+# the last one: dozens of workgroups on every die claim slots of the same few lines at once, so most claims are lost
+# and go on from what the compare-and-swap returned
+@pytest.mark.parametrize("N,k,back,spread", [(32, 8, 3, 0), (64, 16, 0, 0), (100, 33, 7, 3), (300, 64, 9, 12),
+                                             (3000, 1500, 1000, 5)])
 def test_one_home_slot(N, k, back, spread):
     cfg = synth.pool_config("large")
     pool = synth.make_pool(cfg, n_blocks=N, seed=N)
