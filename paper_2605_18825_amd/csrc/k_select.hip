@@ -2693,7 +2693,8 @@ struct BatchSel {
     int32_t ef_lim[16];
     unsigned long long thr[SAE_MAX_QUEUES];
     uint32_t fill;
-    int32_t more;  // a wave has blocks left to read
+    int32_t more;   // a wave has blocks left to read
+    int32_t plain;  // every parameter is finite and no weight negative, so every key is at most that of +inf
 };
 
 // A pass over the cached keys of one instance: fn(q, e) for every evictable
@@ -3122,6 +3123,15 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     const long long base = (long long)inst * N;
     const int kk = inst_k(a, inst, c.max_k);
     load_score_tab(tab, c.state[inst], c);
+    if (tid < SAE_WAVE) {  // each thread the entries it has just written
+        static_assert(SAE_MAX_QUEUES * 8 == SAE_WAVE, "an entry of the weights per lane");
+        const float inf = __uint_as_float(0x7F800000u);
+        bool ok = (tid >> 3) >= Q || __float_as_uint(tab.aw[tid >> 3][tid & 7]) < 0x7F800000u;
+        if (tid < Q) ok = ok && fabsf(tab.mu[tid]) < inf && tab.c[tid] < inf;
+        if (tid == 0) ok = ok && tab.gamma < inf;
+        const bool plain = __all(ok);
+        if (tid == 0) bs.plain = plain ? 1 : 0;
+    }
     if (tid < SAE_MAX_QUEUES) {
         bs.nev[tid] = 0;
         bs.lcnt[tid] = 0;
@@ -3135,9 +3145,11 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     lds_barrier();
 
     uint32_t st = 0;
-    // the streaming path needs its lists (Q x pow2(kk)) and candidates before its list
+    // the streaming path needs its lists (Q x pow2(kk)) and candidates before its
+    // list, and keys of 31 bits (47 of e): negative, infinite or undefined weights
+    // give others, and their blocks are all scored
     const bool stream = list_at >= 0 && Q * kk <= BATCH_STREAM_K && kk > 0 &&
-                        Q * pow2_ge(kk) + BATCH_CAND <= list_at;  // uniform
+                        Q * pow2_ge(kk) + BATCH_CAND <= list_at && bs.plain;  // uniform
     unsigned long long *slist = sh_dyn + (list_at >= 0 ? list_at : 0);
     uint32_t *ckey = reinterpret_cast<uint32_t *>(sh_dyn + (cache_at >= 0 ? cache_at : 0));
     uint8_t *cq = reinterpret_cast<uint8_t *>(ckey + N);

@@ -15,7 +15,7 @@ from paper_2605_18825_amd import api  # noqa: E402
 from paper_2605_18825_amd.pool import DevicePool, SelectBuffers  # noqa: E402
 
 
-def several(n_inst, N, k, flags, layout="large", seed=31, edit=None, k_per=None, mix=None):
+def several(n_inst, N, k, flags, layout="large", seed=31, edit=None, k_per=None, mix=None, **prm):
     """n_inst pools in one context: lists, scores, decisions equal the oracle's."""
     cfg = synth.pool_config(layout, n_blocks=N, k=k, **({} if mix is None else dict(mix=mix)))
     Q = len(cfg["kinds"])
@@ -27,13 +27,13 @@ def several(n_inst, N, k, flags, layout="large", seed=31, edit=None, k_per=None,
             if edit is not None:
                 edit(pool, np.random.default_rng(seed + i))
             dp.fill_instance(i, pool)
-            oc = oracle.OracleCache(N, cfg["kinds"], oracle.Params(Q, mu=cfg["mu"], sigma=cfg["sigma"], K=k))
+            oc = oracle.OracleCache(N, cfg["kinds"], oracle.Params(Q, mu=cfg["mu"], sigma=cfg["sigma"], K=k, **prm))
             oc.bind(pool["last_access"], pool["queue"], oracle.block_type(pool["counts"]), pool["ntok"], pool["ob"],
                     pool["omax"], pool["valid"], pool["ref_count"], pool["parent"], pool["hash"])
             ocs.append(oc)
         dp.bind(ctx)
         api.sae_index_build(ctx)
-        api.sae_set_params(ctx, -1, api.make_params(Q, mu=cfg["mu"], sigma=cfg["sigma"], K=k))
+        api.sae_set_params(ctx, -1, api.make_params(Q, mu=cfg["mu"], sigma=cfg["sigma"], K=k, **prm))
         out = SelectBuffers(n_inst, Q, k)
         now = synth.pools.NOW
         kd = None if k_per is None else torch.as_tensor(np.asarray(k_per, np.int32)).cuda()
@@ -150,6 +150,17 @@ def test_batched_streaming_orders(edit):
     assert set(st) <= {"FUTURE_ACCESS"}
     say("scan: %s" % edit.__name__)
     several(3, 30003, 300, api.SS_ENGINE_SCAN, edit=edit, k_per=[300, 0, 7])
+
+
+# A negative queue or type weight makes negative scores, whose keys (the order of the score's bits) have the top bit
+# set; -0.0 is one of them.  In one queue, in all, and in part of each.
+@pytest.mark.parametrize("alpha,w", [([1, 1, -2, 1, 1], 1), ([-1, -1, -1, -3, -2], 1), (1, [-1, -1, 2, -1, -1]),
+                                     ([1, -0.0, 1, 1, -0.0], 1)])
+@pytest.mark.parametrize("k", [40, 819])
+def test_negative_weights(alpha, w, k):
+    for name, fl in (("batched", api.SS_ENGINE_BATCHED), ("scan", api.SS_ENGINE_SCAN)):
+        say("%s: alpha %s w %s k %d" % (name, alpha, w, k))
+        assert several(2, 20003, k, fl, alpha=alpha, w=w) == []
 
 
 # equal keys in clusters: ranked by comparison, refined by a wave (from 65) or by the workgroup (from 513)
