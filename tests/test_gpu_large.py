@@ -152,3 +152,21 @@ def test_large_equal_key_clusters():
             assert not p.status()
     finally:
         p.close()
+
+
+def test_sparse_sample_on_a_very_large_pool():
+    """12,000,001 blocks, of which the sample holds one in 732: the few bucket
+    ends lie far apart, so that a share of the ranking holds more candidates
+    than fit at once and is split by bucket ends and by value."""
+    cfg = synth.pool_config("large")
+    say("12,000,001 blocks: generating pool")
+    pool = synth.make_pool(cfg, n_blocks=12000001, seed=12)
+    say("12,000,001 blocks: indexing")
+    p = Pair(cfg["kinds"], pool, 700, mu=cfg["mu"], sigma=cfg["sigma"], K=700)
+    try:
+        for k in (16, 256, 700):
+            say("12,000,001 blocks: score_select, k %d" % k)
+            p.select(pool["now"] + k, k)
+        assert not p.status()
+    finally:
+        p.close()
