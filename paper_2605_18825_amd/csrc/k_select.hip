@@ -1075,6 +1075,7 @@ __device__ uint32_t lognormal_dt_floor(const ScoreTab &t, int q, int ty, uint32_
 // spread subset -- and the last one is the bound.  Also writes the scan's
 // filter entries and empties the queue's candidate stripes.
 #define ALL_EST 2048.0
+#define EVEN_CAND 6144.0  // expected candidates from which few buckets are cut evenly into ranges
 #define FIN_G 16  // buckets a workgroup of the ranking takes
 static_assert(SAMPLE_WGS <= SAE_WAVE, "the chunks' counts fit one wave");
 static_assert(SAMPLE_WGS * SAMPLE_CHUNK <= LCAP, "a queue's sampled elements fit the LDS staging area");
@@ -1139,6 +1140,7 @@ __device__ void split_queue(const DevCtx &c, const SelectArgs &a, int q, int ins
     const double f = sample_fraction(c.N);
     const double est = (double)tot / f;
     const uint32_t r = bound_rank(fmin((double)kq, est), f);
+    bool many = false;  // EVEN_CAND candidates expected
     if (kq == 0) {
         // nothing to select: no candidates
     } else if (tot == 0) {
@@ -1184,6 +1186,7 @@ __device__ void split_queue(const DevCtx &c, const SelectArgs &a, int q, int ins
             bound = lds_select_rank(el, (int)K, r, bs);
             rr = r;
         }
+        many = (double)rr >= EVEN_CAND * f;
         // upper ends: the elements <= bound, or every stride-th staged one of them
         const uint32_t stride = rr <= SAE_NBUCKET - 1 ? 1u : (rr + SAE_NBUCKET - 3) / (SAE_NBUCKET - 2);
         const bool sorted = stride == 1u && bs.nsorted >= rr;  // uniform
@@ -1242,10 +1245,19 @@ __device__ void split_queue(const DevCtx &c, const SelectArgs &a, int q, int ins
     lds_barrier();
     const int nb = nb_s;
     if (tid < nb) c.split[iq * SAE_NBUCKET + tid] = spl[tid];
-    // the candidate ranges: a quarter of the buckets each, cut between the
-    // ranking's workgroups (any ascending ends are valid)
+    // the candidate ranges: a quarter of the buckets each (any ascending ends
+    // are valid), cut between the ranking's workgroups, so that each reads one or
+    // two ranges.  With fewer than FIN_G buckets a range such cuts leave one or two
+    // ranges empty and their stripes unused; when so many candidates are expected
+    // that the others' stripes would run over (EVEN_CAND), the cuts lie
+    // between any two buckets.  score_select, us, cut by FIN_G / evenly, by expected
+    // candidates: 43.4 / 45.3 at 1,800 (4,194,304 blocks, k = 16), 58.1 / 62.0 at
+    // 3,600 (8,388,608, 16), 83.9 / 85.8 at 5,100 (12,000,000, 16), 75.0 / 75.5 at
+    // 6,700 (8,388,608, 1,024), 86.6 / 84.5 at 6,600 (12,000,000, 256), 83.9 / 75.3
+    // at 8,200 (16,777,216, 256)
     if (tid < SAE_PARTS) {
-        const int b = (nb * (tid + 1) / SAE_PARTS + FIN_G / 2) / FIN_G * FIN_G;
+        int b = nb * (tid + 1) / SAE_PARTS;
+        if (nb >= SAE_PARTS * FIN_G || !many) b = (b + FIN_G / 2) / FIN_G * FIN_G;
         c.cend[iq * SAE_PARTS + tid] = (tid == SAE_PARTS - 1 || b >= nb) ? ~0ull : (b > 0 ? spl[b - 1] : 0ull);
     }
     if (tid == 0) {

@@ -157,7 +157,8 @@ def test_large_equal_key_clusters():
 def test_sparse_sample_on_a_very_large_pool():
     """12,000,001 blocks, of which the sample holds one in 732: the few bucket
     ends lie far apart, so that a share of the ranking holds more candidates
-    than fit at once and is split by bucket ends and by value."""
+    than fit at once and is split by bucket ends and by value, and (from k =
+    256 on) the candidate ranges are cut between any two buckets."""
     cfg = synth.pool_config("large")
     say("12,000,001 blocks: generating pool")
     pool = synth.make_pool(cfg, n_blocks=12000001, seed=12)

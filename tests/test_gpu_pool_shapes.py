@@ -163,6 +163,15 @@ def test_negative_weights(alpha, w, k):
         assert several(2, 20003, k, fl, alpha=alpha, w=w) == []
 
 
+# Few buckets per queue (28 to 64 of them with one block in 64 sampled, a single one where the sample holds none):
+# the cuts of the candidate ranges on both sides of the ranking's workgroups.
+@pytest.mark.parametrize("k", [1, 64, 150, 200, 260])
+@pytest.mark.parametrize("mix", [None, [0.0001, 0.4, 0.5996, 0.00002, 0.0999]])
+def test_scan_few_buckets(k, mix):
+    say("scan: 1,048,576 blocks, k %d, mix %s" % (k, mix))
+    assert several(1, 1048576, k, api.SS_ENGINE_SCAN, mix=mix) == []
+
+
 # equal keys in clusters: ranked by comparison, refined by a wave (from 65) or by the workgroup (from 513)
 @pytest.mark.parametrize("size", [64, 65, 130, 512, 513, 1500])
 def test_scan_clusters_of_equal_keys(size):
