@@ -504,77 +504,58 @@ __device__ int merge_decision_lds(const unsigned long long *lists, int Pe, const
     return n1 + min(rest, total);
 }
 
-// Sort, ascending, of T / S segments of S elements in LDS (S a power of two,
-// T <= 4 blockDim.x; the elements of a segment distinct, unused slots ~0 at
-// its end), blockDim.x = SEL_THREADS.  Runs of 64 (or whole segments shorter
-// than that) are sorted in registers, one element per lane, by a bitonic
-// network; then every element's place is its own in its run plus its counts
-// of smaller elements in the segment's other runs, searched eight at a time.
-// Two barriers whatever the size: 256 x 4 took 10 us as runs of 256 sorted by
-// one wave each.  All threads call.
+// Sort, ascending, of T / S segments of S elements in LDS (S a power of two up
+// to RANK_SEG, T <= blockDim.x = SEL_THREADS; the elements of a segment distinct,
+// unused slots ~0 at its end), one element per thread.  Runs of 64 (or whole
+// segments shorter than that) are sorted in registers by a bitonic network; then
+// every element's place is its own in its run plus its counts of smaller
+// elements in the segment's other runs, searched side by side.  Two barriers
+// whatever the size.  All threads call.
+#define RANK_SEG 256
 __device__ void sort_segments_rank(unsigned long long *a, int T, int S)
 {
-    constexpr int MAXE = 4;
+    constexpr int NR = RANK_SEG / SAE_WAVE;
     const int tid = threadIdx.x, lane = lane_id();
     const int R = S < SAE_WAVE ? S : SAE_WAVE;  // elements of a run
-    unsigned long long x[MAXE];
-#pragma unroll
-    for (int u = 0; u < MAXE; ++u) {
-        const int i = tid + u * SEL_THREADS;
-        x[u] = i < T ? a[i] : ~0ull;
-        if (u * SEL_THREADS >= T) continue;  // uniform
+    const int s0 = tid & ~(S - 1);
+    unsigned long long x = tid < T ? a[tid] : ~0ull;
+    if (s0 < T) {  // (longer segments than a wave: uniform)
 #pragma unroll 1
         for (int k = 2; k <= R; k <<= 1) {
 #pragma unroll 1
             for (int j = k >> 1; j > 0; j >>= 1) {
-                const unsigned long long y = shfl_xor_u64(x[u], j);
+                const unsigned long long y = shfl_xor_u64(x, j);
                 const bool low = ((lane & j) == 0) == ((lane & k) == 0 || k == R);
-                x[u] = ((x[u] < y) == low) ? x[u] : y;
+                x = ((x < y) == low) ? x : y;
             }
         }
-        if (i < T) a[i] = x[u];
-    }
-    if (S <= SAE_WAVE) {
-        lds_barrier();
-        return;
+        if (tid < T) a[tid] = x;
     }
     lds_barrier();
-    int rank[MAXE];
-    const int nr = S / SAE_WAVE;  // runs per segment
+    if (S <= SAE_WAVE) return;
+    int rank = lane;
+    if (s0 < T) {  // wave-uniform
+        const int nr = S / SAE_WAVE, own = (tid - s0) / SAE_WAVE;
+        int l[NR];
 #pragma unroll
-    for (int u = 0; u < MAXE; ++u) {
-        const int i = tid + u * SEL_THREADS;
-        rank[u] = lane;
-        if (u * SEL_THREADS >= T) continue;  // uniform
-        const int s0 = (i < T ? i : 0) & ~(S - 1);
-        const int own = ((i < T ? i : 0) - s0) / SAE_WAVE;
-#pragma unroll 1
-        for (int g = 0; g < nr; g += 8) {  // uniform
-            int l[8];
+        for (int w = 0; w < NR; ++w) l[w] = 0;
 #pragma unroll
-            for (int w = 0; w < 8; ++w) l[w] = 0;
+        for (int st = SAE_WAVE; st > 0; st >>= 1) {
 #pragma unroll
-            for (int st = SAE_WAVE; st > 0; st >>= 1) {
-#pragma unroll
-                for (int w = 0; w < 8; ++w) {
-                    if (g + w < nr) {  // uniform
-                        const int t = l[w] + st;  // st = 64: the whole run is smaller
-                        const int tc = t <= SAE_WAVE ? t : SAE_WAVE;  // an unconditional read
-                        const unsigned long long v = a[s0 + (g + w) * SAE_WAVE + tc - 1];
-                        l[w] = (t <= SAE_WAVE && v < x[u]) ? t : l[w];
-                    }
+            for (int w = 0; w < NR; ++w) {
+                if (w < nr) {  // uniform
+                    const int t = l[w] + st;  // st = 64: the whole run is smaller
+                    const int tc = t <= SAE_WAVE ? t : SAE_WAVE;  // an unconditional read
+                    const unsigned long long v = a[s0 + w * SAE_WAVE + tc - 1];
+                    l[w] = (t <= SAE_WAVE && v < x) ? t : l[w];
                 }
             }
-#pragma unroll
-            for (int w = 0; w < 8; ++w) rank[u] += (g + w < nr && g + w != own) ? l[w] : 0;
         }
+#pragma unroll
+        for (int w = 0; w < NR; ++w) rank += (w < nr && w != own) ? l[w] : 0;
     }
     lds_barrier();
-#pragma unroll
-    for (int u = 0; u < MAXE; ++u) {
-        const int i = tid + u * SEL_THREADS;
-        if (i < T && x[u] != ~0ull) a[(i & ~(S - 1)) + rank[u]] = x[u];
-    }
+    if (s0 < T && x != ~0ull) a[s0 + rank] = x;
     lds_barrier();
 }
 
@@ -3386,7 +3367,11 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     }
     if (st) atomicOr(&bs.st, st);
     lds_barrier();
-    if (Q * Pe <= 4 * SEL_THREADS) sort_segments_rank(lists, Q * Pe, Pe);
+    // One element per thread and up to four runs per list: by ranks.  4,096 blocks,
+    // by ranks / by merged runs of 256: 30.0 / 31.3 us at 3 lists of 256, 37.8 / 37.0
+    // at 5 of 256 (two elements per thread), 48.4 / 41.6 at 3 of 512, 67.7 / 48.9 at
+    // 5 of 512; by ranks / by the bitonic network: 27.7 / 30.5 at 3 of 128
+    if (Pe <= RANK_SEG && Q * Pe <= SEL_THREADS) sort_segments_rank(lists, Q * Pe, Pe);
     else if (Pe >= 256 && 2 * Q * Pe <= dyn_elems) sort_segments_lds(lists, Q * Pe, Pe);
     else bitonic_sort_segments(lists, Q, Pe, Pe);
     if (tid < Q) cnt_s[tid] = (int32_t)min(bs.need[tid], (uint32_t)P);

@@ -252,3 +252,23 @@ def test_scan_takes_every_block(N, sizes):
 def test_batched_small_pools(N, k):
     say("batched: 4 instances of %d blocks, k %d" % (N, k))
     several(4, N, k, api.SS_ENGINE_BATCHED)
+
+
+# the list sorts: whole lists in a wave, up to four runs a list and one element per thread by ranks, then merged runs
+# (or, for one short list more than fits, the bitonic network); and the merge of the lists
+@pytest.mark.parametrize("kinds", ["L", "RS", "ELR", "ELLR", "ESLLR", "LSRLSRLS"])
+@pytest.mark.parametrize("k", [31, 64, 65, 128, 129, 200, 256, 257, 512, 700, 1500])
+def test_batched_list_sizes(kinds, k):
+    names = dict(E=api.KIND_EVICT_FIRST, L=api.KIND_LOGNORMAL, R=api.KIND_RECENCY, S=api.KIND_STRUCTURAL)
+    Q = len(kinds)
+    pool = synth.make_pool(synth.pool_config("large"), n_blocks=6007, seed=50 * Q + k)
+    rng = np.random.default_rng(k)
+    pool["queue"] = rng.integers(0, Q, 6007).astype(pool["queue"].dtype)
+    p = Pair([names[x] for x in kinds], pool, k, mu=[5.0 + 0.5 * q for q in range(Q)], sigma=[1.0] * Q, K=k)
+    try:
+        for t in (0, 300):
+            say("batched: queues %s, k %d" % (kinds, k))
+            p.select(pool["now"] + t, k, flags=api.SS_ENGINE_BATCHED)
+        assert not p.status()
+    finally:
+        p.close()
