@@ -3389,7 +3389,14 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
         a.count[(long long)inst * Q + tid] = cnt_s[tid];
         c.sel_count[(long long)inst * Q + tid] = cnt_s[tid];
     }
-    const int d = merge_decision_lds(lists, Pe, cnt_s, Q, c.ef_queue, kk, a.decision + (long long)inst * c.max_k);
+    // The merge with all searches side by side reads every list for every element
+    // and costs by rounds of the workgroup; the other one skips lists and stops
+    // early.  4,096 blocks, us, side by side / one after the other: 25.0 / 26.3 at 3
+    // lists of 64, 29.6 / 30.9 at 3 of 256, 36.4 / 36.7 at 5 of 256 (256 caches 40.6 /
+    // 42.4), 41.3 / 38.8 at 3 of 512, 48.4 / 45.2 at 5 of 512, 58.0 / 48.7 at 3 of 1,024
+    int32_t *dec = a.decision + (long long)inst * c.max_k;
+    const int d = Q * Pe <= SEL_THREADS + SEL_THREADS / 4 ? merge_decision_lds(lists, Pe, cnt_s, Q, c.ef_queue, kk, dec)
+                                                          : merge_decision(lists, Pe, cnt_s, Q, c.ef_queue, kk, dec);
     if (tid == 0) {
         a.decision_count[inst] = d;
         if (!(a.flags & SAE_SS_CASCADE)) commit_bookkeeping(c.state[inst], d, (a.flags & SAE_SS_COMMIT) != 0);
