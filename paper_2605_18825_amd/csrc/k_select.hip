@@ -2666,14 +2666,32 @@ __global__ void __launch_bounds__(FIN_THREADS) k_final(DevCtx c, SelectArgs a, i
 #define BATCH_CAND 2048  // candidate elements beyond the largest lists in LDS
 #define BATCH_RANK 512   // candidates ranked by comparison (an LDS read of a wave per pair row: 1,500 took 16 us)
 #define BATCH_LQ 128     // blocks a wave's scoring list holds: < 64 left + 64 pushed
-#define BATCH_LDS_N 8192       // largest pool whose keys are cached in LDS
-#define BATCH_STREAM_N 16384   // smallest pool that is streamed
-#define BATCH_STREAM_K 4096    // largest Q k that is streamed
+#define BATCH_LDS_N 16384      // largest pool whose keys are cached in LDS, where they fit
+#define BATCH_STREAM_N 16384   // smallest pool that is streamed (with a small k: batch_streams)
 #define BATCH_ROUND (4 * SEL_THREADS)             // blocks a workgroup reads per round
 #define BATCH_LIST 10240       // elements of the streaming list: a cut one (BATCH_CUT) and what each wave may
 #define BATCH_CUT 4096         //   add before it looks again (a batch of 256 blocks, 2 x 63 held back, 3 of the tail)
 static_assert(BATCH_CUT + BATCH_ROUND + 2 * SEL_THREADS <= BATCH_LIST, "a batch of every wave fits a cut list");
-static_assert(BATCH_STREAM_K <= BATCH_CUT, "a list cut exactly fits");
+// Whether a pool of N blocks is streamed for k victims of Q queues.  Scoring and
+// caching every block costs by N; streaming costs less per block, but a cut of
+// the list (4 to 10 us) comes the more often the more of it the lists' first k
+// elements take, and a queue adds to that by more than its k.  The line is about
+// where both measured alike over 3 to 5 queues and 32 to 256 caches (streamed /
+// cached in device memory, us): 65,536 blocks, k (Q + 2) = 1,300: 114 / 156;
+// 3,900 (k = 780 of 3): 158 / 152; 5,000: 179 / 166; 40,000 blocks, 1,400: 97 / 111; 2,400:
+// 103 / 111; 2,800 (555 of 3): 123 / 119; 30,001 blocks, 1,400: 87 / 88; 2,000: 91 / 89; 27,000
+// blocks, 960: 75 / 75; 24,000 blocks, 220 to 390: 61 to 64 / 61 to 64; 830: 72 / 66; 17,001
+// blocks, 85: 55 / 50.  Four rounds of BATCH_ROUND end with the second cut, which
+// makes a pool of up to as many blocks the cheaper one to stream; its keys fit LDS,
+// though, and up to 900 the two are within 7 % of each other (k = 16 of 3: 41.7 / 43.6,
+// 64 of 3: 47.8 / 46.2, 128 of 5: 56.5 / 58.6), beyond that LDS wins (200 of 5: 64.0 / 60.0).
+__device__ __forceinline__ bool batch_streams(int N, int Q, int k)
+{
+    const int few = (N - 22000) / 5, most = N / 16;
+    const int lim = N <= 4 * BATCH_ROUND ? 900 : (few < most ? few : most);
+    return k > 0 && k * (Q + 2) <= lim;
+}
+static_assert(BATCH_IPT * SEL_THREADS / 16 <= BATCH_CUT, "a list cut exactly fits");
 #define BATCH_LQ_BYTES (SEL_THREADS / SAE_WAVE * 2 * 3 * BATCH_LQ * 4)  // the first pass's lists (48 KiB)
 struct BatchSel {
     unsigned long long lo[SAE_MAX_QUEUES], hi[SAE_MAX_QUEUES];
@@ -3149,8 +3167,8 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
     // the streaming path needs its lists (Q x pow2(kk)) and candidates before its
     // list, and keys of 31 bits (47 of e): negative, infinite or undefined weights
     // give others, and their blocks are all scored
-    const bool stream = list_at >= 0 && Q * kk <= BATCH_STREAM_K && kk > 0 &&
-                        Q * pow2_ge(kk) + BATCH_CAND <= list_at && bs.plain;  // uniform
+    const bool stream = list_at >= 0 && batch_streams(N, Q, kk) && Q * pow2_ge(kk) + BATCH_CAND <= list_at &&
+                        bs.plain;  // uniform
     unsigned long long *slist = sh_dyn + (list_at >= 0 ? list_at : 0);
     uint32_t *ckey = reinterpret_cast<uint32_t *>(sh_dyn + (cache_at >= 0 ? cache_at : 0));
     uint8_t *cq = reinterpret_cast<uint8_t *>(ckey + N);
@@ -3855,13 +3873,13 @@ hipError_t launch_select_batched(const DevCtx &c, const SelectArgs &a, hipStream
     // call's k fits before it; 256 x 65,536 blocks, k = 256, max_k = 4,096:
     // 130 us and 174 MB of traffic, cached 160 us and 453 MB)
     const size_t before = lds < most - (size_t)BATCH_LIST * 8 ? lds : most - (size_t)BATCH_LIST * 8;
+    const size_t keys = lds + ((size_t)c.N * 5 + 15) / 16 * 16;
+    if (c.N <= BATCH_LDS_N && keys <= most) cache_at = (int)(lds / 8);
     if (c.N >= BATCH_STREAM_N && before >= h && before >= (size_t)BATCH_LQ_BYTES) {
         list_at = (int)(before / 8);
         if (lds < before + (size_t)BATCH_LIST * 8) lds = before + (size_t)BATCH_LIST * 8;
-    } else if (c.N <= BATCH_LDS_N && lds + (size_t)c.N * 5 <= most) {
-        cache_at = (int)(lds / 8);
-        lds += ((size_t)c.N * 5 + 15) / 16 * 16;
     }
+    if (cache_at >= 0 && lds < keys) lds = keys;  // a pool of both sizes uses one or the other of a call's two
     const int dyn_elems = (int)(lds / 8);
     hipError_t e = allow_lds((const void *)k_batched, lds);
     if (e != hipSuccess) return e;

@@ -152,15 +152,32 @@ def test_batched_streaming_orders(edit):
     several(3, 30003, 300, api.SS_ENGINE_SCAN, edit=edit, k_per=[300, 0, 7])
 
 
+# on both sides of the rule for streaming (5 queues) and of the largest pool cached in LDS
+@pytest.mark.parametrize("N,k", [(12001, 50), (16383, 128), (16384, 128), (16384, 129), (16385, 20), (24003, 57),
+                                 (24003, 58), (30002, 228), (30002, 229), (40001, 357), (40001, 358), (65536, 585),
+                                 (65536, 586)])
+def test_batched_streaming_rule(N, k):
+    say("batched: 2 instances of %d blocks, k %d" % (N, k))
+    assert several(2, N, k, api.SS_ENGINE_BATCHED) == []
+
+
+@pytest.mark.parametrize("edit", [newest_last, newest_first, clusters, late_queue, edges])
+@pytest.mark.parametrize("N,k", [(40003, 350), (65533, 500)])
+def test_batched_streaming_orders_large(edit, N, k):
+    say("batched: %s, %d blocks, k %d" % (edit.__name__, N, k))
+    st = several(3, N, k, api.SS_ENGINE_BATCHED, edit=edit, k_per=[k, 0, 7])
+    assert set(st) <= {"FUTURE_ACCESS"}
+
+
 # A negative queue or type weight makes negative scores, whose keys (the order of the score's bits) have the top bit
 # set; -0.0 is one of them.  In one queue, in all, and in part of each.
 @pytest.mark.parametrize("alpha,w", [([1, 1, -2, 1, 1], 1), ([-1, -1, -1, -3, -2], 1), (1, [-1, -1, 2, -1, -1]),
                                      ([1, -0.0, 1, 1, -0.0], 1)])
-@pytest.mark.parametrize("k", [40, 819])
+@pytest.mark.parametrize("k", [40, 300])
 def test_negative_weights(alpha, w, k):
     for name, fl in (("batched", api.SS_ENGINE_BATCHED), ("scan", api.SS_ENGINE_SCAN)):
         say("%s: alpha %s w %s k %d" % (name, alpha, w, k))
-        assert several(2, 20003, k, fl, alpha=alpha, w=w) == []
+        assert several(2, 40003, k, fl, alpha=alpha, w=w) == []
 
 
 # Few buckets per queue (28 to 64 of them with one block in 64 sampled, a single one where the sample holds none):
