@@ -1056,7 +1056,7 @@ __device__ uint32_t lognormal_dt_floor(const ScoreTab &t, int q, int ty, uint32_
 // spread subset -- and the last one is the bound.  Also writes the scan's
 // filter entries and empties the queue's candidate stripes.
 #define ALL_EST 2048.0
-#define EVEN_CAND 6144.0  // expected candidates from which few buckets are cut evenly into ranges
+#define EVEN_CAND 6144    // expected candidates from which few buckets are cut evenly into ranges
 #define FIN_G 16  // buckets a workgroup of the ranking takes
 static_assert(SAMPLE_WGS <= SAE_WAVE, "the chunks' counts fit one wave");
 static_assert(SAMPLE_WGS * SAMPLE_CHUNK <= LCAP, "a queue's sampled elements fit the LDS staging area");
@@ -1121,7 +1121,6 @@ __device__ void split_queue(const DevCtx &c, const SelectArgs &a, int q, int ins
     const double f = sample_fraction(c.N);
     const double est = (double)tot / f;
     const uint32_t r = bound_rank(fmin((double)kq, est), f);
-    bool many = false;  // EVEN_CAND candidates expected
     if (kq == 0) {
         // nothing to select: no candidates
     } else if (tot == 0) {
@@ -1167,7 +1166,6 @@ __device__ void split_queue(const DevCtx &c, const SelectArgs &a, int q, int ins
             bound = lds_select_rank(el, (int)K, r, bs);
             rr = r;
         }
-        many = (double)rr >= EVEN_CAND * f;
         // upper ends: the elements <= bound, or every stride-th staged one of them
         const uint32_t stride = rr <= SAE_NBUCKET - 1 ? 1u : (rr + SAE_NBUCKET - 3) / (SAE_NBUCKET - 2);
         const bool sorted = stride == 1u && bs.nsorted >= rr;  // uniform
@@ -1238,6 +1236,8 @@ __device__ void split_queue(const DevCtx &c, const SelectArgs &a, int q, int ins
     // at 8,200 (16,777,216, 256)
     if (tid < SAE_PARTS) {
         int b = nb * (tid + 1) / SAE_PARTS;
+        // (so few buckets are the sampled ends cut in four)
+        const bool many = (long long)nb * c.N >= 4ll * EVEN_CAND * SAMPLE_WGS * SAMPLE_CHUNK;
         if (nb >= SAE_PARTS * FIN_G || !many) b = (b + FIN_G / 2) / FIN_G * FIN_G;
         c.cend[iq * SAE_PARTS + tid] = (tid == SAE_PARTS - 1 || b >= nb) ? ~0ull : (b > 0 ? spl[b - 1] : 0ull);
     }
