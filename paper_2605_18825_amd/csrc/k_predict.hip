@@ -351,11 +351,12 @@ hipError_t predict_scratch(float **out)
 }
 
 // Up to 2,048 rows the 128-wide tiles are at most 128 workgroups, half of the
-// compute units, and a workgroup's time is its bytes over what one unit is fed
-// (about 50-70 KB/us): 64-wide tiles halve those bytes and quadruple the
-// workgroups.  Layer 1 at d = 4,096, 64- against 128-wide: 5.2 / 10.5 us at 1
-// row, 6.7 / 12.3 at 256, 7.9 / 12.9 at 1,024, 13.2 / 13.6 at 2,048, 22.8 /
-// 15.8 at 4,096 (there the 64-wide tiles move twice the bytes).
+// compute units, and a workgroup's time is its bytes over what its unit is fed:
+// 64-wide tiles halve those bytes and quadruple the workgroups.  Layer 1 at d =
+// 4,096 on hidden states that no cache holds, 64- against 128-wide: 6.4 / 12.1 us at
+// 1 and 256 rows, 7.8 / 12.1 at 1,024, 14.2 / 14.0 at 2,048, 30.9 / 17.8 at 4,096 (there the
+// 64-wide tiles move twice the bytes).  A unit is fed 42 KB/us (512 KB in 12.1
+// us) while a quarter of them work and 29 KB/us when all do: together 7.5 TB/s.
 constexpr int L1_64_MAX_ROWS = 2048;
 
 hipError_t launch_predict(int n, int d, const uint16_t *h, const uint16_t *w1, const float *b1, const float *w2,

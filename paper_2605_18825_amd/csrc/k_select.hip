@@ -14,7 +14,7 @@
 //  * batched (pools of <= 65,536 blocks): one workgroup of 1024 threads per
 //    instance does scoring, the radix select of all queues, the sort and the
 //    merge in one launch; it caches every key (small and middle pools) or
-//    streams the pool through the exact filter (from BATCH_STREAM_N blocks on).
+//    streams the pool through the exact filter (large pools, small k: batch_streams).
 #include <hip/hip_ext.h>
 
 #include "sae_internal.h"
@@ -1357,7 +1357,8 @@ __global__ void __launch_bounds__(SEL_THREADS) k_match_prep(DevCtx c, SelectArgs
 // and its ends are only further cuts.)  By one workgroup of the scan's launch,
 // beside the scan: every workgroup of the ranking needs the merged ends, and
 // merging them there took each 3 to 4 us before it read its first candidate
-// (k_final of a step of 262,144 blocks 16.0 us, now 13.4; the scan is 0.3 us longer).
+// (k_final of a step of 262,144 blocks 16.0 us, now 13.4; this workgroup alone
+// makes the scan 0.3 us longer).
 // eq: Q SAE_NBUCKET values of LDS.
 __device__ __forceinline__ void merge_ends(const DevCtx &c, int inst, unsigned long long *eq)
 {
@@ -1735,7 +1736,9 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(DevCtx c, SelectArgs a)
     // range's candidates are then in some tens of workgroups, and in one stripe
     // per workgroup they filled those and the overflow list, and with them a
     // ranking wave's region (k_final 13 to 385 us, 52 on average, now 16,
-    // on such a pool of 4,194,304 blocks)
+    // on such a pool of 4,194,304 blocks).  The ranges, the pieces and the workgroup
+    // that merges the ends cost the scan of that pool 2.1 us together (16.9 -> 19.0;
+    // k_final 18.7 -> 16.1 for it), of larger ones 1 to 3
     constexpr int PUT = SAE_MAX_QUEUES * SCAN_CB / SCAN_THREADS;
     static_assert(PUT * SCAN_THREADS == SAE_MAX_QUEUES * SCAN_CB, "a thread's share of the buffers");
     uint32_t cell[PUT], pos[PUT];  // queue and range, position among this workgroup's; cell ~0: none
@@ -2003,8 +2006,7 @@ __device__ __forceinline__ void fin_wave_refine(unsigned long long *st2, uint32_
 // by one wave, which holds them in registers, so that 16 clusters are refined
 // at a time, and above that by the workgroup.  One after the other by the
 // workgroup, at about 1.5 us each, the clusters of a serving step of 4,194,304
-// blocks took half of k_final (33.5 us, 26
-// with single waves).  A range holding more than fits is split in two (by its bucket ends, or by
+// blocks took half of k_final (33.5 us, 26 with single waves).  A range holding more than fits is split in two (by its bucket ends, or by
 // value once it has a single bucket) and the halves are ranked in order.  All
 // threads call; `ends` is in LDS.
 template <typename Out>
@@ -2188,7 +2190,9 @@ __device__ void fin_rank(const DevCtx &c, int inst, const FinInfo &f, uint32_t s
                     stack[sp_s++] = a2;
                     stack[sp_s++] = a1;
                 } else {
-                    stop_s = 1;  // cannot happen: each split at least halves a 64-bit range
+                    // cannot happen: a split leaves one range more pending, and from
+                    // FIN_STACK / 3 of them on each halves a 64-bit range
+                    stop_s = 1;
                 }
             }
         } else {
@@ -2637,9 +2641,11 @@ __global__ void __launch_bounds__(FIN_THREADS) k_final(DevCtx c, SelectArgs a, i
 // over a set of elements that holds every queue's k smallest, gathered in one
 // of two ways:
 //  * whole pool: every evictable block is scored (Eq. 1-3) and its key and
-//    queue cached, in LDS for a small pool (at most BATCH_LDS_N blocks), else
-//    in device memory (5 B per block);
-//  * streaming (BATCH_STREAM_N blocks and more, Q k <= BATCH_STREAM_K): the
+//    queue cached (5 B per block), in LDS up to BATCH_LDS_N blocks where that
+//    fits beside max_k's lists (us, LDS / device memory: 8,193 blocks, k = 64 of 5
+//    queues 35.9 / 38.6, 256 caches of 16,000 blocks 47.7 / 51.7; it is never the slower
+//    one), else in device memory;
+//  * streaming (BATCH_STREAM_N blocks and more, where batch_streams says so): the
 //    pool is read once, in rounds of 4,096 blocks, and an LDS list keeps the
 //    elements that can still be among their queue's k smallest.  After 1 and
 //    4 rounds, and whenever the list runs full, every queue's list is cut at a
@@ -3126,7 +3132,8 @@ __device__ void batch_stream(const DevCtx &c, const SelectArgs &a, int inst, Bat
     }
 }
 
-__global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a, int P, int dyn_elems, int list_at, int cache_at)
+__global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a, int P, int dyn_elems, int list_at,
+                                                         int cache_at)
 {
     // hist [Q][SAE_BINS] u32, later lists [Q][Pe] + candidates; from list_at the
     // streaming list, from cache_at the LDS key cache (-1: none)
@@ -3176,145 +3183,145 @@ __global__ void __launch_bounds__(SEL_THREADS) k_batched(DevCtx c, SelectArgs a,
         batch_stream(c, a, inst, bs, tab, kk, hist, slist, hist, st);
         batch_start(bs, Q, kk, 47);
     } else {
-    // first pass: score, cache, count, smallest and largest key per queue
-    uint32_t cnt_r[SAE_MAX_QUEUES], mn_r[SAE_MAX_QUEUES], mx_r[SAE_MAX_QUEUES];
+        // first pass: score, cache, count, smallest and largest key per queue
+        uint32_t cnt_r[SAE_MAX_QUEUES], mn_r[SAE_MAX_QUEUES], mx_r[SAE_MAX_QUEUES];
 #pragma unroll
-    for (int q = 0; q < SAE_MAX_QUEUES; ++q) {
-        cnt_r[q] = 0;
-        mn_r[q] = 0xFFFFFFFFu;
-        mx_r[q] = 0;
-    }
-    {
-        // A wave's lanes hold blocks of every queue kind, and Eq. 1 (ln,
-        // erfc) and Eq. 2 are long: scored in place, every wave would run
-        // both.  So the blocks of log-normal and structural queues are queued
-        // per wave in LDS with their fields (the dynamic LDS is free until
-        // the digit passes) and scored 64 at a time, one kind per wave-wide
-        // step; the other kinds cost a few operations and are scored in place.
-        // The next step's loads go out before this step is scored.
-        uint32_t *wq = reinterpret_cast<uint32_t *>(sh_dyn) + (tid / SAE_WAVE) * 2 * 3 * BATCH_LQ;
-        uint32_t nq0 = 0, nq1 = 0;  // fill of the log-normal and structural lists (wave-uniform)
-        const unsigned long long lt = lanemask_lt();
-        // the queues of each list's kind and of the kinds scored in place
-        // (bit q): a block's counts only touch those
-        uint32_t qm_ln = 0, qm_st = 0;
-        for (int qq = 0; qq < Q; ++qq) {
-            qm_ln |= (tab.kind[qq] == SAE_KIND_LOGNORMAL) ? 1u << qq : 0u;
-            qm_st |= (tab.kind[qq] == SAE_KIND_STRUCTURAL) ? 1u << qq : 0u;
+        for (int q = 0; q < SAE_MAX_QUEUES; ++q) {
+            cnt_r[q] = 0;
+            mn_r[q] = 0xFFFFFFFFu;
+            mx_r[q] = 0;
         }
-        const uint32_t qm_rest = ((1u << Q) - 1u) & ~(qm_ln | qm_st);
-        auto finish = [&](int b, uint32_t m, uint32_t key, bool ev, uint32_t qmask) {
-            const int q = meta_queue(m);
-            if (ev) {
+        {
+            // A wave's lanes hold blocks of every queue kind, and Eq. 1 (ln,
+            // erfc) and Eq. 2 are long: scored in place, every wave would run
+            // both.  So the blocks of log-normal and structural queues are queued
+            // per wave in LDS with their fields (the dynamic LDS is free until
+            // the digit passes) and scored 64 at a time, one kind per wave-wide
+            // step; the other kinds cost a few operations and are scored in place.
+            // The next step's loads go out before this step is scored.
+            uint32_t *wq = reinterpret_cast<uint32_t *>(sh_dyn) + (tid / SAE_WAVE) * 2 * 3 * BATCH_LQ;
+            uint32_t nq0 = 0, nq1 = 0;  // fill of the log-normal and structural lists (wave-uniform)
+            const unsigned long long lt = lanemask_lt();
+            // the queues of each list's kind and of the kinds scored in place
+            // (bit q): a block's counts only touch those
+            uint32_t qm_ln = 0, qm_st = 0;
+            for (int qq = 0; qq < Q; ++qq) {
+                qm_ln |= (tab.kind[qq] == SAE_KIND_LOGNORMAL) ? 1u << qq : 0u;
+                qm_st |= (tab.kind[qq] == SAE_KIND_STRUCTURAL) ? 1u << qq : 0u;
+            }
+            const uint32_t qm_rest = ((1u << Q) - 1u) & ~(qm_ln | qm_st);
+            auto finish = [&](int b, uint32_t m, uint32_t key, bool ev, uint32_t qmask) {
+                const int q = meta_queue(m);
+                if (ev) {
 #pragma unroll
-                for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq) {
-                    if (qq >= Q) break;  // uniform
-                    if (!((qmask >> qq) & 1u)) continue;  // uniform
-                    cnt_r[qq] += (qq == q) ? 1u : 0u;
-                    mn_r[qq] = (qq == q) ? min(mn_r[qq], key) : mn_r[qq];
-                    mx_r[qq] = (qq == q) ? max(mx_r[qq], key) : mx_r[qq];
+                    for (int qq = 0; qq < SAE_MAX_QUEUES; ++qq) {
+                        if (qq >= Q) break;  // uniform
+                        if (!((qmask >> qq) & 1u)) continue;  // uniform
+                        cnt_r[qq] += (qq == q) ? 1u : 0u;
+                        mn_r[qq] = (qq == q) ? min(mn_r[qq], key) : mn_r[qq];
+                        mx_r[qq] = (qq == q) ? max(mx_r[qq], key) : mx_r[qq];
+                    }
                 }
-            }
-            if (cache_at >= 0) {  // uniform
-                ckey[b] = key;
-                cq[b] = ev ? (uint8_t)(q + 1) : (uint8_t)0;
-            } else {
-                c.bkey[base + b] = key;
-                c.bq[base + b] = ev ? (uint8_t)(q + 1) : (uint8_t)0;
-            }
-        };
-        // Score the lists: each one that holds 64 (or, at the end, whatever
-        // it holds).  One call site, so that the two long key functions are
-        // compiled once.
-        auto drain = [&](bool final) {
+                if (cache_at >= 0) {  // uniform
+                    ckey[b] = key;
+                    cq[b] = ev ? (uint8_t)(q + 1) : (uint8_t)0;
+                } else {
+                    c.bkey[base + b] = key;
+                    c.bq[base + b] = ev ? (uint8_t)(q + 1) : (uint8_t)0;
+                }
+            };
+            // Score the lists: each one that holds 64 (or, at the end, whatever
+            // it holds).  One call site, so that the two long key functions are
+            // compiled once.
+            auto drain = [&](bool final) {
 #pragma unroll 1
-            for (int which = 0; which < 2; ++which) {
-                uint32_t &nq = which == 0 ? nq0 : nq1;
-                const uint32_t n = final ? nq : (nq >= SAE_WAVE ? (uint32_t)SAE_WAVE : 0u);
-                if (n == 0) continue;  // uniform
-                nq -= n;
-                const uint32_t *w = wq + which * 3 * BATCH_LQ;
-                const bool act = (uint32_t)lane < n;
-                const uint32_t p = nq + (act ? (uint32_t)lane : 0u);
-                const int32_t la = (int32_t)w[p];
-                const uint32_t off = w[BATCH_LQ + p], mb = w[2 * BATCH_LQ + p];
-                const uint32_t m = mb & 0xFFFFu;
-                if (act) {
-                    const uint32_t key = which == 0 ? key_lognormal(a.now, la, m, tab, st)
-                                                    : key_structural(a.now, la, m, off, tab, st);
-                    finish((int)(mb >> 16), m, key, true, which == 0 ? qm_ln : qm_st);
+                for (int which = 0; which < 2; ++which) {
+                    uint32_t &nq = which == 0 ? nq0 : nq1;
+                    const uint32_t n = final ? nq : (nq >= SAE_WAVE ? (uint32_t)SAE_WAVE : 0u);
+                    if (n == 0) continue;  // uniform
+                    nq -= n;
+                    const uint32_t *w = wq + which * 3 * BATCH_LQ;
+                    const bool act = (uint32_t)lane < n;
+                    const uint32_t p = nq + (act ? (uint32_t)lane : 0u);
+                    const int32_t la = (int32_t)w[p];
+                    const uint32_t off = w[BATCH_LQ + p], mb = w[2 * BATCH_LQ + p];
+                    const uint32_t m = mb & 0xFFFFu;
+                    if (act) {
+                        const uint32_t key = which == 0 ? key_lognormal(a.now, la, m, tab, st)
+                                                        : key_structural(a.now, la, m, off, tab, st);
+                        finish((int)(mb >> 16), m, key, true, which == 0 ? qm_ln : qm_st);
+                    }
                 }
-            }
-        };
-        // Each lane takes blocks tid + 1024 j (consecutive lanes, consecutive
-        // blocks: coalesced loads and key-cache stores), four j per step; the
-        // next step's loads are issued before this step is scored (indices
-        // past the pool load block 0).
-        const int nj = (N + SEL_THREADS - 1) / SEL_THREADS;
-        auto ld = [&](int j0, int32_t (&l)[4], uint32_t (&mm)[4], uint32_t (&o)[4]) {
+            };
+            // Each lane takes blocks tid + 1024 j (consecutive lanes, consecutive
+            // blocks: coalesced loads and key-cache stores), four j per step; the
+            // next step's loads are issued before this step is scored (indices
+            // past the pool load block 0).
+            const int nj = (N + SEL_THREADS - 1) / SEL_THREADS;
+            auto ld = [&](int j0, int32_t (&l)[4], uint32_t (&mm)[4], uint32_t (&o)[4]) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int b = tid + (j0 + u) * SEL_THREADS;
-                const long long g = base + (((j0 + u) < nj && b < N) ? b : 0);
-                l[u] = c.la[g];
-                mm[u] = c.meta[g];
-                o[u] = c.off[g];
-            }
-        };
-        int32_t lc[4], ln[4];
-        uint32_t mc[4], mn2[4], oc[4], on[4];
-        ld(0, lc, mc, oc);
-        for (int j0 = 0; j0 < nj; j0 += 4) {  // uniform
-            ld(j0 + 4, ln, mn2, on);
+                for (int u = 0; u < 4; ++u) {
+                    const int b = tid + (j0 + u) * SEL_THREADS;
+                    const long long g = base + (((j0 + u) < nj && b < N) ? b : 0);
+                    l[u] = c.la[g];
+                    mm[u] = c.meta[g];
+                    o[u] = c.off[g];
+                }
+            };
+            int32_t lc[4], ln[4];
+            uint32_t mc[4], mn2[4], oc[4], on[4];
+            ld(0, lc, mc, oc);
+            for (int j0 = 0; j0 < nj; j0 += 4) {  // uniform
+                ld(j0 + 4, ln, mn2, on);
 #pragma unroll 1
-            for (int e = 0; e < 4; ++e) {
-                // one block per lane: scored in place, or queued
-                const int b = tid + (j0 + e) * SEL_THREADS;
-                const bool in = (j0 + e) < nj && b < N;
-                const int32_t la = e == 0 ? lc[0] : (e == 1 ? lc[1] : (e == 2 ? lc[2] : lc[3]));
-                const uint32_t off = e == 0 ? oc[0] : (e == 1 ? oc[1] : (e == 2 ? oc[2] : oc[3]));
-                const uint32_t m = e == 0 ? mc[0] : (e == 1 ? mc[1] : (e == 2 ? mc[2] : mc[3]));
-                const bool ev = in && meta_evictable(m) && meta_queue(m) < Q;
-                const int kind = ev ? tab.kind[meta_queue(m)] : -1;
-                const bool to0 = kind == SAE_KIND_LOGNORMAL, to1 = kind == SAE_KIND_STRUCTURAL;
-                if (in && !to0 && !to1) finish(b, m, ev ? key_cheap(kind, a.now, la, m, tab, st) : 0u, ev, qm_rest);
-                const unsigned long long m0 = __ballot(to0), m1 = __ballot(to1);
-                if (to0 || to1) {
-                    const uint32_t p = to0 ? nq0 + (uint32_t)__popcll(m0 & lt) : nq1 + (uint32_t)__popcll(m1 & lt);
-                    uint32_t *w = wq + (to0 ? 0 : 3 * BATCH_LQ);
-                    w[p] = (uint32_t)la;
-                    w[BATCH_LQ + p] = off;
-                    w[2 * BATCH_LQ + p] = m | ((uint32_t)b << 16);
+                for (int e = 0; e < 4; ++e) {
+                    // one block per lane: scored in place, or queued
+                    const int b = tid + (j0 + e) * SEL_THREADS;
+                    const bool in = (j0 + e) < nj && b < N;
+                    const int32_t la = e == 0 ? lc[0] : (e == 1 ? lc[1] : (e == 2 ? lc[2] : lc[3]));
+                    const uint32_t off = e == 0 ? oc[0] : (e == 1 ? oc[1] : (e == 2 ? oc[2] : oc[3]));
+                    const uint32_t m = e == 0 ? mc[0] : (e == 1 ? mc[1] : (e == 2 ? mc[2] : mc[3]));
+                    const bool ev = in && meta_evictable(m) && meta_queue(m) < Q;
+                    const int kind = ev ? tab.kind[meta_queue(m)] : -1;
+                    const bool to0 = kind == SAE_KIND_LOGNORMAL, to1 = kind == SAE_KIND_STRUCTURAL;
+                    if (in && !to0 && !to1) finish(b, m, ev ? key_cheap(kind, a.now, la, m, tab, st) : 0u, ev, qm_rest);
+                    const unsigned long long m0 = __ballot(to0), m1 = __ballot(to1);
+                    if (to0 || to1) {
+                        const uint32_t p = to0 ? nq0 + (uint32_t)__popcll(m0 & lt) : nq1 + (uint32_t)__popcll(m1 & lt);
+                        uint32_t *w = wq + (to0 ? 0 : 3 * BATCH_LQ);
+                        w[p] = (uint32_t)la;
+                        w[BATCH_LQ + p] = off;
+                        w[2 * BATCH_LQ + p] = m | ((uint32_t)b << 16);
+                    }
+                    nq0 += (uint32_t)__popcll(m0);
+                    nq1 += (uint32_t)__popcll(m1);
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    drain(false);
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
                 }
-                nq0 += (uint32_t)__popcll(m0);
-                nq1 += (uint32_t)__popcll(m1);
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                drain(false);
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                lc[u] = ln[u];
-                mc[u] = mn2[u];
-                oc[u] = on[u];
+                for (int u = 0; u < 4; ++u) {
+                    lc[u] = ln[u];
+                    mc[u] = mn2[u];
+                    oc[u] = on[u];
+                }
+            }
+            drain(true);  // what the lists still hold
+        }
+#pragma unroll
+        for (int q = 0; q < SAE_MAX_QUEUES; ++q) {
+            if (q >= Q) break;  // uniform
+            const uint32_t v = wave_sum(cnt_r[q]), lo = wave_min(mn_r[q]), hi = wave_max(mx_r[q]);
+            if (lane == 0 && v) {
+                atomicAdd(&bs.nev[q], v);
+                atomicMin(&bs.mn[q], lo);
+                atomicMax(&bs.mx[q], hi);
             }
         }
-        drain(true);  // what the lists still hold
-    }
-#pragma unroll
-    for (int q = 0; q < SAE_MAX_QUEUES; ++q) {
-        if (q >= Q) break;  // uniform
-        const uint32_t v = wave_sum(cnt_r[q]), lo = wave_min(mn_r[q]), hi = wave_max(mx_r[q]);
-        if (lane == 0 && v) {
-            atomicAdd(&bs.nev[q], v);
-            atomicMin(&bs.mn[q], lo);
-            atomicMax(&bs.mx[q], hi);
-        }
-    }
-    lds_barrier();
-    batch_start(bs, Q, kk, 0);
+        lds_barrier();
+        batch_start(bs, Q, kk, 0);
     }
     if (tid == 0) {  // list segments of Pe = pow2 >= the largest need
         uint32_t mx = 1;
@@ -3865,7 +3872,8 @@ hipError_t launch_select_batched(const DevCtx &c, const SelectArgs &a, hipStream
     const size_t h = (size_t)c.Q * SAE_BINS * 4, l = ((size_t)c.Q * P + BATCH_CAND) * 8;
     size_t lds = h > l ? h : l;
     if (lds < (size_t)BATCH_LQ_BYTES) lds = BATCH_LQ_BYTES;  // the first pass's scoring lists
-    // a large pool adds the streaming list, a small one the key cache, where they fit
+    // a large pool adds the streaming list, a small one the key cache, where they
+    // fit; one that has both (of the two sizes at once) uses one of them per call
     int list_at = -1, cache_at = -1;
     const size_t most = 156 * 1024;  // of the 160 KiB, the rest for the static part
     // (the list and lists of max_k are never there together: with a large max_k
@@ -3879,7 +3887,7 @@ hipError_t launch_select_batched(const DevCtx &c, const SelectArgs &a, hipStream
         list_at = (int)(before / 8);
         if (lds < before + (size_t)BATCH_LIST * 8) lds = before + (size_t)BATCH_LIST * 8;
     }
-    if (cache_at >= 0 && lds < keys) lds = keys;  // a pool of both sizes uses one or the other of a call's two
+    if (cache_at >= 0 && lds < keys) lds = keys;
     const int dyn_elems = (int)(lds / 8);
     hipError_t e = allow_lds((const void *)k_batched, lds);
     if (e != hipSuccess) return e;

@@ -175,9 +175,12 @@ sae_status sae_create(const sae_config *cfg, sae_ctx **out)
     d.scan_gx = scan_grid_x(d.n_inst, d.N);
     bool ok = dev_alloc(c, &d.state, I) && dev_alloc(c, &d.status, 1) &&
               dev_alloc(c, &d.index, I * c->index_slots) && dev_alloc(c, &d.ring, I * d.ring_cap) &&
-              dev_alloc(c, &d.gtab, I * c->ghost_slots) && dev_alloc(c, &d.thr, I * Q) && dev_alloc(c, &d.sent, I * 64) && dev_alloc(c, &d.eflim, I * 16) &&
-              dev_alloc(c, &d.split, I * Q * SAE_NBUCKET) && dev_alloc(c, &d.nsplit, I * Q) && dev_alloc(c, &d.mend, I * Q * SAE_NBUCKET) && dev_alloc(c, &d.n_mend, I) &&
-              dev_alloc(c, &d.cand, I * Q * 2 * SAE_LCAP) && dev_alloc(c, &d.stripe_n, I * Q * (SAE_CELLS + 1)) && dev_alloc(c, &d.cend, I * Q * SAE_PARTS) &&
+              dev_alloc(c, &d.gtab, I * c->ghost_slots) && dev_alloc(c, &d.thr, I * Q) &&
+              dev_alloc(c, &d.sent, I * 64) && dev_alloc(c, &d.eflim, I * 16) &&
+              dev_alloc(c, &d.split, I * Q * SAE_NBUCKET) && dev_alloc(c, &d.nsplit, I * Q) &&
+              dev_alloc(c, &d.mend, I * Q * SAE_NBUCKET) && dev_alloc(c, &d.n_mend, I) &&
+              dev_alloc(c, &d.cand, I * Q * 2 * SAE_LCAP) && dev_alloc(c, &d.stripe_n, I * Q * (SAE_CELLS + 1)) &&
+              dev_alloc(c, &d.cend, I * Q * SAE_PARTS) &&
               dev_alloc(c, &d.cpart, I * SAE_CSLOTS * SAE_CF_STRIDE) &&
               dev_alloc(c, &d.samp, I * SAE_SAMPLE_WGS * SAE_SAMPLE_CHUNK) &&
               dev_alloc(c, &d.samp_qn, I * SAE_SAMPLE_WGS * SAE_MAX_QUEUES) &&

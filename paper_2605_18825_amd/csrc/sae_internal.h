@@ -27,7 +27,8 @@
 #define SAE_NBUCKET 256  // buckets
 #define SAE_LCAP 16384   // candidates kept per (instance, queue)
 // The scan divides a queue's candidates into SAE_PARTS ranges of value with
-// about as many candidates each (a workgroup of the ranking then reads the one
+// about as many candidates each where they are many (few buckets may leave a
+// range or two empty: split_queue; a workgroup of the ranking then reads the one
 // or two ranges it ranks, not all candidates) and appends a range's to one of
 // SAE_STRIPES stripes of SAE_STRIPE_CAP slots (one device atomic per workgroup
 // and range, spread over the stripes so that few workgroups meet on one
@@ -140,7 +141,7 @@ struct DevCtx {
     unsigned long long *samp;  // [n_inst][SAE_SAMPLE_WGS][SAE_SAMPLE_CHUNK] sampled (key << 32 | id)
     uint32_t *samp_qn;         // [n_inst][SAE_SAMPLE_WGS][SAE_MAX_QUEUES] sampled elements per chunk and queue
     uint32_t *prep_done;       // [n_inst] sampling workgroups of sae_match_select finished, ever (wraps)
-    uint32_t *sel_stats;       // [n_inst][Q][4] last pool scan: evictable, candidates, beyond a stripe, slow path
+    uint32_t *sel_stats;       // [n_inst][Q][4] last pool scan: evictable, candidates, beyond the overflow list, slow path
     unsigned long long *split; // [n_inst][Q][SAE_NBUCKET] bucket upper ends, ascending; the last is thr
     int32_t *nsplit;           // [n_inst][Q] buckets (0: no candidates)
     unsigned long long *mend;  // [n_inst][Q SAE_NBUCKET] the decision's bucket ends: all queues' but the
@@ -260,7 +261,10 @@ __device__ __forceinline__ uint32_t hash_home(unsigned long long h, uint32_t mas
 // one load per step that was two to ten dependent round trips of 0.5 us or more.
 // Serving step of 262,144 blocks, 1,024 evicted and added: k_insert_a 7.5 us in groups of 8
 // (the first group 8 and single steps after it 9.5, the first group 4 11.3,
-// single steps 13.8), k_commit 6.9 (9.2 in single steps).
+// single steps 13.8), k_commit 6.9 (9.2 in single steps).  Eight slots from the home
+// slot on lie in two lines of 128 bytes seven times out of eight: on a fresh pool,
+// where most sequences end at once and the tables come from HBM, k_commit of 4,096
+// victims is the slower for it, 6.1 -> 7.3 us; after some steps it is 9.4 -> 8.2.
 #define PROBE_G 8
 struct ProbeGroup {
     unsigned long long h[PROBE_G];
