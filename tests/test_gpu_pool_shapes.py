@@ -89,6 +89,22 @@ def test_equal_keys_in_id_order(N, k, mix):
     assert several(1, N, k, api.SS_ENGINE_SCAN, edit=edit, mix=mix) == []
 
 
+@pytest.mark.parametrize("N,k,mix", [(300001, 1000, None), (1048576, 300, [0.96, 0.01, 0.01, 0.01, 0.01])])
+def test_equal_keys_with_outliers(N, k, mix):
+    """As above, with a few blocks decades older or newer and a few partly
+    filled ones, so that splits by value also meet ranges that are empty but
+    for their ends."""
+    def edit(pool, rng):
+        pool["last_access"][:] = synth.pools.NOW - 5000
+        pool["last_access"][rng.choice(N, 40, replace=False)] = synth.pools.NOW - 900000
+        pool["last_access"][rng.choice(N, 40, replace=False)] = synth.pools.NOW - 1
+        pool["ntok"][rng.choice(N, 40, replace=False)] = 15
+        pool["ntok"][rng.choice(N, 10, replace=False)] = 1
+
+    say("equal keys and outliers: %d blocks, k %d" % (N, k))
+    assert several(1, N, k, api.SS_ENGINE_SCAN, edit=edit, mix=mix) == []
+
+
 def test_largest_k_without_fallback():
     """k = 8,192 on 4M blocks: about 16,000 candidates per queue, more than the
     stripes alone hold; their overflow list takes the rest and the exact slow
@@ -135,7 +151,7 @@ def edges(pool, rng):
     pool["ob"] = np.where(rng.random(n) < 0.5, pool["omax"], 0).astype(np.int32)
 
 
-# the streaming path of the batched engine: from 16,384 blocks on and Q k <= 4,096, several cuts, every alignment
+# the batched engine around and above 16,384 blocks, streamed (small k) and cached, every alignment
 @pytest.mark.parametrize("N,k", [(16384, 1), (16385, 64), (16387, 819), (16383, 64), (40001, 819), (65535, 257),
                                  (65536, 256), (65536, 820)])
 def test_batched_streaming_sizes(N, k):
@@ -289,3 +305,10 @@ def test_batched_list_sizes(kinds, k):
         assert not p.status()
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("n_inst,N,k", [(300, 1501, 40), (270, 24601, 60)])
+def test_batched_more_caches_than_compute_units(n_inst, N, k):
+    """Workgroups that start when others have ended, with the key cache in LDS and streamed."""
+    say("batched: %d caches of %d blocks" % (n_inst, N))
+    assert several(n_inst, N, k, api.SS_ENGINE_BATCHED) == []
