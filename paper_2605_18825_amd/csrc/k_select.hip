@@ -3879,7 +3879,7 @@ hipError_t launch_select_batched(const DevCtx &c, const SelectArgs &a, hipStream
     // (the list and lists of max_k are never there together: with a large max_k
     // the list takes part of their room, and the kernel streams where the
     // call's k fits before it; 256 x 65,536 blocks, k = 256, max_k = 4,096:
-    // 130 us and 174 MB of traffic, cached 160 us and 453 MB)
+    // 127 us and 174 MB of traffic, cached 160 us and 453 MB)
     const size_t before = lds < most - (size_t)BATCH_LIST * 8 ? lds : most - (size_t)BATCH_LIST * 8;
     const size_t keys = lds + ((size_t)c.N * 5 + 15) / 16 * 16;
     if (c.N <= BATCH_LDS_N && keys <= most) cache_at = (int)(lds / 8);
