@@ -266,15 +266,16 @@ __device__ __forceinline__ uint32_t hash_home(unsigned long long h, uint32_t mas
 // where most sequences end at once and the tables come from HBM, k_commit of 4,096
 // victims is the slower for it, 6.1 -> 7.3 us; after some steps it is 9.4 -> 8.2.
 #define PROBE_G 8
+template <int G>
 struct ProbeGroup {
-    unsigned long long h[PROBE_G];
+    unsigned long long h[G];
 };
-template <typename Slot>
-__device__ __forceinline__ ProbeGroup probe_load(const Slot *tab, uint32_t mask, uint32_t s)
+template <int G, typename Slot>
+__device__ __forceinline__ ProbeGroup<G> probe_load(const Slot *tab, uint32_t mask, uint32_t s)
 {
-    ProbeGroup v;
+    ProbeGroup<G> v;
 #pragma unroll
-    for (int t = 0; t < PROBE_G; ++t) v.h[t] = tab[(s + (uint32_t)t) & mask].hash;
+    for (int t = 0; t < G; ++t) v.h[t] = tab[(s + (uint32_t)t) & mask].hash;
     return v;
 }
 __device__ __forceinline__ int probe_limit(uint32_t mask)
@@ -283,13 +284,14 @@ __device__ __forceinline__ int probe_limit(uint32_t mask)
 }
 
 // Of a group: the first slot that can be claimed (*v its hash, empty or
-// deleted), PROBE_G if there is none.
-__device__ __forceinline__ int probe_free(const ProbeGroup &a, unsigned long long *v)
+// deleted), G if there is none.
+template <int G>
+__device__ __forceinline__ int probe_free(const ProbeGroup<G> &a, unsigned long long *v)
 {
-    int at = PROBE_G;
+    int at = G;
     unsigned long long e = SAE_EMPTY_HASH;
 #pragma unroll
-    for (int t = PROBE_G - 1; t >= 0; --t)
+    for (int t = G - 1; t >= 0; --t)
         if (a.h[t] == SAE_EMPTY_HASH || a.h[t] == SAE_TOMB_HASH) {
             at = t;
             e = a.h[t];
@@ -298,13 +300,14 @@ __device__ __forceinline__ int probe_free(const ProbeGroup &a, unsigned long lon
     return at;
 }
 
-// The first slot that holds h or ends the search (*end: an empty one), PROBE_G if there is none.
-__device__ __forceinline__ int probe_hash(const ProbeGroup &a, unsigned long long h, bool *end)
+// The first slot that holds h or ends the search (*end: an empty one), G if there is none.
+template <int G>
+__device__ __forceinline__ int probe_hash(const ProbeGroup<G> &a, unsigned long long h, bool *end)
 {
-    int at = PROBE_G;
+    int at = G;
     bool e = false;
 #pragma unroll
-    for (int t = PROBE_G - 1; t >= 0; --t)
+    for (int t = G - 1; t >= 0; --t)
         if (a.h[t] == h || a.h[t] == SAE_EMPTY_HASH) {
             at = t;
             e = a.h[t] != h;
@@ -319,16 +322,16 @@ __device__ __forceinline__ int probe_hash(const ProbeGroup &a, unsigned long lon
 // hash from this die's L2.  A slot that holds a hash by then, or is lost a second
 // time, is passed by (it was not empty then, so no search ends at it), so every
 // round moves on and the search ends after the probe limit.
-template <typename Slot>
+template <int G, typename Slot>
 __device__ __forceinline__ long long probe_claim(Slot *tab, uint32_t mask, unsigned long long h, int p)
 {
     const uint32_t home = hash_home(h, mask);
     const int lim = probe_limit(mask);
     while (p < lim) {
         unsigned long long v;
-        const int at = probe_free(probe_load(tab, mask, home + (uint32_t)p), &v);
+        const int at = probe_free(probe_load<G>(tab, mask, home + (uint32_t)p), &v);
         p += at;
-        if (at == PROBE_G || p >= lim) continue;
+        if (at == G || p >= lim) continue;
         const uint32_t s = (home + (uint32_t)p) & mask;
         const unsigned long long w = atomicCAS(&tab[s].hash, v, h);
         if (w == v) return (long long)s;
@@ -347,7 +350,7 @@ __device__ __forceinline__ void index_erase(IndexSlot *tab, uint32_t mask, unsig
     const int lim = probe_limit(mask);
     while (p < lim) {
         bool end;
-        const int at = probe_hash(probe_load(tab, mask, home + (uint32_t)p), h, &end);
+        const int at = probe_hash(probe_load<PROBE_G>(tab, mask, home + (uint32_t)p), h, &end);
         p += at;
         if (at == PROBE_G) continue;
         if (end || p >= lim) return;
@@ -376,7 +379,8 @@ __device__ __forceinline__ void commit_victim(const DevCtx &c, int inst, int j, 
     IndexSlot *tab = c.index + (long long)inst * ((long long)c.index_mask + 1);
     GhostSlot *gt = c.gtab + (long long)inst * ((long long)c.ghost_mask + 1);
     const uint32_t si = hash_home(h, c.index_mask), sg = hash_home(h, c.ghost_mask);
-    const ProbeGroup vi = probe_load(tab, c.index_mask, si), vg = probe_load(gt, c.ghost_mask, sg);
+    const auto vi = probe_load<PROBE_G>(tab, c.index_mask, si);
+    const auto vg = probe_load<PROBE_G>(gt, c.ghost_mask, sg);
     const bool has_p = p >= 0 && p < c.N;
     const long long gp = (long long)inst * c.N + (has_p ? p : 0);
     const bool hashed = !SAE_HASH_RESERVED(h);  // a reserved hash was never indexed
@@ -405,7 +409,7 @@ __device__ __forceinline__ void commit_victim(const DevCtx &c, int inst, int j, 
     if (og == vf) {
         gt[sf].ring = rp;
     } else {  // no free slot among the first, or lost it
-        const long long at = probe_claim(gt, c.ghost_mask, h, tg);
+        const long long at = probe_claim<PROBE_G>(gt, c.ghost_mask, h, tg);
         if (at >= 0) gt[at].ring = rp;
         else set_status(c.status, SAE_ST_GHOST_FULL);
     }

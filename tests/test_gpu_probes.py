@@ -71,3 +71,33 @@ def test_one_home_slot(N, k, back, spread):
         assert not p.status()
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("n", [524287, 524288])
+def test_bulk_add_and_build(n):
+    """Both group sizes of the probes (from 524,288 blocks on another one): a
+    cache filled by one Add(), then indexed anew, against the oracle."""
+    N = 600011
+    cfg = synth.pool_config("large")
+    pool = synth.make_pool(cfg, n_blocks=N, seed=n)
+    pool["valid"][:] = False
+    pool["parent"][:] = -1
+    pool["ref_count"][:] = 0
+    say("bulk: %d blocks" % n)
+    p = Pair(cfg["kinds"], pool, 64, mu=cfg["mu"], sigma=cfg["sigma"])
+    try:
+        ids = np.random.default_rng(n).permutation(N)[:n].astype(np.int32)
+        p.insert(ids, pool["hash"][ids], np.full(n, -1, np.int32), pool["last_access"][ids], pool["queue"][ids],
+                 pool["counts"][ids], pool["ntok"][ids], pool["ob"][ids], pool["omax"][ids])
+        R, L = synth.make_requests(pool["chains"], 64, 32, 0.9, 9)
+        say("bulk: added, matching and selecting")
+        p.prefix_match(R, L, pool["now"], api.PM_STATS)
+        p.select(pool["now"], 64)
+        p.check_counters()
+        assert not p.status()
+        say("bulk: indexing anew")
+        api.sae_index_build(p.ctx)
+        p.prefix_match(R, L, pool["now"] + 1, 0)
+        assert not p.status()
+    finally:
+        p.close()
