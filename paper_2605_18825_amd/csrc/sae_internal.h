@@ -255,8 +255,9 @@ __device__ __forceinline__ uint32_t hash_home(unsigned long long h, uint32_t mas
     return (uint32_t)(z >> 32) & mask;
 }
 
-// PROBE_G slots of a probe sequence (linear from the home slot, as every
-// lookup of the block index and of recently_evicted walks it), their hashes
+// G slots of a probe sequence (linear from the home slot, as every lookup of the
+// block index and of recently_evicted walks it), PROBE_G of them in a step's
+// commit and Add() and fewer where tables are filled in bulk, their hashes
 // loaded together: a wave waits for the longest sequence of its lanes, and with
 // one load per step that was two to ten dependent round trips of 0.5 us or more.
 // Serving step of 262,144 blocks, 1,024 evicted and added: k_insert_a 7.5 us in groups of 8
